@@ -294,6 +294,7 @@ GemmArgs gemm(int M, int N, int K, const float* A, int64_t sam, int64_t sak, int
   g.beta = beta;
   g.gelu_u = nullptr;
   g.halfA = g.halfB = g.halfC = 0;
+  g.rowwise = 0;
   g.Cin = nullptr;
   g.r1c = nullptr;
   g.r1tsh = g.r1dsh = g.r1H = g.r1round = 0;
@@ -339,6 +340,11 @@ bool lower_forward(trace_model* m, int l, const float* X, float* Xn, int64_t N, 
   float* V = kp ? kp->V : m->lv;
   float* O = kp ? kp->O : m->lo;
   bool ok = true;
+  auto gemm = [](auto... x) {
+    GemmArgs g = ::gemm(x...);
+    g.rowwise = 1;
+    return g;
+  };
   ok = launch_gemm(gemm(R, D, D, X, D, 1, rX, th + L.at(P_WQ, l), D, 1, rb, Q, D, 0.f), ws, cap, s) && ok;
   ok = launch_gemm(gemm(R, D, D, X, D, 1, rX, th + L.at(P_WK, l), D, 1, rb, K, D, 0.f), ws, cap, s) && ok;
   ok = launch_gemm(gemm(R, D, D, X, D, 1, rX, th + L.at(P_WV, l), D, 1, rb, V, D, 0.f), ws, cap, s) && ok;

@@ -371,6 +371,8 @@ bool launch_gemm(const GemmArgs& g0, float* ws, int64_t ws_cap, hipStream_t s) {
   if (g0.M <= 0 || g0.N <= 0) return true;
   // bf16 storage points on at least one side: register-staged bf16 GEMM
   if (launch_bgemm(g0, nullptr, ws, ws_cap, s)) return true;
+  // fp32 operands on both sides: the k-split kernel of small products
+  if (launch_fgemm(g0, nullptr, ws, ws_cap, s)) return true;
   // the kernels below use fp32 operands and results, and read B as stored
   if (g0.halfA || g0.halfB || g0.halfC || g0.r1c) return false;
   GemmArgs g = g0;
@@ -417,7 +419,7 @@ bool launch_gemm(const GemmArgs& g0, float* ws, int64_t ws_cap, hipStream_t s) {
 
 void launch_gemm2(const GemmArgs& g, const GemmArgs& g2, float* ws, int64_t ws_cap, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return;
-  if (launch_bgemm(g, &g2, ws, ws_cap, s)) return;
+  if (launch_bgemm(g, &g2, ws, ws_cap, s) || launch_fgemm(g, &g2, ws, ws_cap, s)) return;
   launch_gemm(g, ws, ws_cap, s);
   GemmArgs h = g2;
   h.C = g.C;

@@ -111,6 +111,9 @@ struct GemmArgs {
   // C is written as bf16 (rounded to nearest even; C then points at bf16
   // elements); needs beta 0, and the product is not split over k
   int halfC;
+  // forward products: a row's sum over k must not depend on the batch (M), so the
+  // kernel that splits k for small batches (fgemm.hip) is not used
+  int rowwise;
 };
 // Deterministic: split-K partials are summed in a fixed order.  The split count
 // depends only on (M, N, K, ws_cap); gemm_ws_floats(M, N, K) floats let it
@@ -128,6 +131,9 @@ void launch_splitk_reduce(const float* ws, int splits, int M, int N, float* C, i
 // force: 0 the kernel the shape calls for, 1 the 128-tile kernel, 2 the 256-tile kernel
 bool launch_bgemm(const GemmArgs& g, const GemmArgs* g2, float* ws, int64_t ws_cap, hipStream_t s, int force = 0);
 int64_t bgemm_ws_floats(int M, int N, int K);
+// fgemm.hip: small products of fp32 operands; false (nothing launched) when the
+// product is not one it takes
+bool launch_fgemm(const GemmArgs& g, const GemmArgs* g2, float* ws, int64_t ws_cap, hipStream_t s);
 
 void launch_colsum(const float* in, int64_t rows, int64_t cols, int64_t ld, float* out, float beta, float* ws,
                    hipStream_t s);
