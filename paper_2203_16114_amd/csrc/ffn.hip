@@ -315,6 +315,228 @@ __global__ __launch_bounds__(512) void k_ffn_head(FfnArgs a) {
   ffn_head_out<BF, D, MB, KEEP, YSTR>(a, Ys, red, zy, tg);
 }
 
+// --------------------------------------------- few windows, fp32 operands ----
+// k_ffn_lat: the arithmetic of k_ffn_head, value for value in the same order,
+// for launches whose window tiles would leave most CUs idle.  There the time is
+// one workgroup's serial chain: per chunk of 128 features D/16 + 8 k-steps, each
+// waiting for weight fragments requested one step before (an L2 round trip of
+// about 500 cycles against 32-128 cycles of MFMAs), on a tile of 128 windows of
+// which a batch of 16 fills one eighth.  Here a workgroup takes 16 or 32 windows,
+// all its waves split the features, and the weight fragments of a whole product
+// are requested one product ahead (W2's chunk before GEMM1, the next W1 chunk
+// right after it, the head's before the last barrier), so a chunk waits once;
+// G is double-buffered (one barrier per chunk).  The log-sum-exp runs 16 threads
+// per window over the logits staged in LDS, summed in k_ffn_head's order.
+// Measured (us, k_ffn_head -> this): d = 64, F = 256, k = 2, 16 to 2048 windows
+// 53 -> 13; d = 128, F = 512, k = 2, 512 windows 156 -> 29 (kept activations 172 ->
+// 34); d = 256, F = 1024, k = 2, 512 windows 329 -> 102.
+template <int D, int NFC, bool KEEP>
+__global__ __launch_bounds__(D >= 128 ? 512 : 256) void k_ffn_lat(FfnArgs a) {
+  typedef Mma<false> M;
+  constexpr int NW = D >= 128 ? 8 : 4, NT = 64 * NW, FC = 128, MB = 16 * NFC;
+  constexpr int RF1 = FC / (16 * NW), RF2 = D / (16 * NW), HF = 16 / NW;
+  constexpr int KD = D / 16, KC = FC / 16, NB2 = D / 16;
+  constexpr int YSTR = D * 4 + 16, GSTR = FC * 4 + 16, ZSTR = 260;
+  static_assert(RF1 >= 1 && RF2 >= 1, "shape");
+  __shared__ __align__(16) unsigned char Ys[MB * YSTR];
+  __shared__ __align__(16) unsigned char Gs[2][MB * GSTR];
+  __shared__ __align__(16) float Zs[MB * ZSTR];
+  __shared__ int tg[MB];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lg = lane >> 4, lc = lane & 15;
+  const int64_t tile0 = (int64_t)blockIdx.x * MB;
+  const int64_t N = a.w.N;
+  const int F = a.F, NB1 = F / 16;
+  const int d0 = wave * (D / NW), f0 = wave * (FC / NW);
+  const uint4* W1p = a.W1;
+  const uint4* W2p = a.W2;
+  uint4 wa[KD][RF1], wb[KC][RF2];
+  auto load1 = [&](const uint4* W, int c0) {
+#pragma unroll
+    for (int ks = 0; ks < KD; ++ks)
+#pragma unroll
+      for (int rf = 0; rf < RF1; ++rf) wa[ks][rf] = W[(ks * NB1 + (c0 + f0) / 16 + rf) * 64 + lane];
+  };
+  load1(W1p, 0);
+
+  // Y^T: lane holds Y[nf*16 + lc][d0 + rf*16 + 4*lg + r]
+  f32x4 y[RF2][NFC];
+#pragma unroll
+  for (int nf = 0; nf < NFC; ++nf) {
+    const int64_t n = tile0 + nf * 16 + lc;
+#pragma unroll
+    for (int rf = 0; rf < RF2; ++rf) {
+      if (n < N) {
+        const float4 v = *reinterpret_cast<const float4*>(a.h0 + n * D + d0 + rf * 16 + 4 * lg);
+        y[rf][nf] = f32x4{v.x, v.y, v.z, v.w};
+      } else {
+        y[rf][nf] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+  }
+  if (tid < MB) {
+    const int64_t n = tile0 + tid;
+    int v = 0;
+    if (n < N) {
+      v = a.w.streams[target_offset(a.w, n)];
+      if (KEEP) a.ktgt[n] = v;
+    }
+    tg[tid] = v;
+  }
+  const unsigned char* yrow = Ys + lc * YSTR + lg * 16;
+  auto put_y = [&](int rep) {
+#pragma unroll
+    for (int nf = 0; nf < NFC; ++nf) {
+      const int m = nf * 16 + lc;
+      const int64_t n = tile0 + m;
+#pragma unroll
+      for (int rf = 0; rf < RF2; ++rf) {
+        const int dd = d0 + rf * 16 + 4 * lg;
+        if (KEEP && n < N) put4((float*)a.kY + ((int64_t)rep * N + n) * D + dd, y[rf][nf]);
+        put4((float*)(Ys + m * YSTR) + dd, y[rf][nf]);
+      }
+    }
+  };
+  for (int rep = 0; rep < a.k; ++rep) {
+    put_y(rep);
+    __syncthreads();
+    for (int c0 = 0; c0 < F; c0 += FC) {
+#pragma unroll
+      for (int ks = 0; ks < KC; ++ks)
+#pragma unroll
+        for (int rf = 0; rf < RF2; ++rf) wb[ks][rf] = W2p[((c0 / 16 + ks) * NB2 + d0 / 16 + rf) * 64 + lane];
+      f32x4 u[RF1][NFC];
+#pragma unroll
+      for (int rf = 0; rf < RF1; ++rf)
+#pragma unroll
+        for (int nf = 0; nf < NFC; ++nf) u[rf][nf] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < KD; ++ks) {
+        uint4 bb[NFC];
+#pragma unroll
+        for (int nf = 0; nf < NFC; ++nf) bb[nf] = *(const uint4*)(yrow + nf * 16 * YSTR + ks * 64);
+#pragma unroll
+        for (int rf = 0; rf < RF1; ++rf)
+#pragma unroll
+          for (int nf = 0; nf < NFC; ++nf) M::run(u[rf][nf], wa[ks][rf], bb[nf]);
+      }
+      if (c0 + FC < F)
+        load1(W1p, c0 + FC);
+      else if (rep + 1 < a.k)
+        load1(W1p + a.wstride, 0);
+      unsigned char* Gb = Gs[(c0 / FC) & 1];  // (F / FC is even: the buffers alternate across repeats too)
+#pragma unroll
+      for (int nf = 0; nf < NFC; ++nf) {
+        const int m = nf * 16 + lc;
+        const int64_t n = tile0 + m;
+#pragma unroll
+        for (int rf = 0; rf < RF1; ++rf) {
+          const int fl = f0 + rf * 16 + 4 * lg;
+          if (KEEP && n < N)
+            *reinterpret_cast<float4*>(a.kU + ((int64_t)rep * N + n) * F + c0 + fl) =
+                make_float4(u[rf][nf][0], u[rf][nf][1], u[rf][nf][2], u[rf][nf][3]);
+          f32x4 gv;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) gv[r] = gelu_as(u[rf][nf][r]);
+          put4((float*)(Gb + m * GSTR) + fl, gv);
+        }
+      }
+      // the other buffer's readers (the chunk before) are past this barrier's
+      // predecessor only once they have multiplied it
+      __syncthreads();
+      const unsigned char* grow = Gb + lc * GSTR + lg * 16;
+#pragma unroll
+      for (int ks = 0; ks < KC; ++ks) {
+        uint4 bb[NFC];
+#pragma unroll
+        for (int nf = 0; nf < NFC; ++nf) bb[nf] = *(const uint4*)(grow + nf * 16 * GSTR + ks * 64);
+#pragma unroll
+        for (int rf = 0; rf < RF2; ++rf)
+#pragma unroll
+          for (int nf = 0; nf < NFC; ++nf) M::run(y[rf][nf], wb[ks][rf], bb[nf]);
+      }
+    }
+    W1p += a.wstride;
+    W2p += a.wstride;
+  }
+  // head: wave w forms logits [w*256/NW, (w+1)*256/NW)
+  constexpr int ZP = KD < 8 ? KD : 8;  // k-steps of head weights in flight
+  uint4 wz[ZP][HF];
+  auto loadz = [&](int ks) {
+#pragma unroll
+    for (int hf = 0; hf < HF; ++hf) wz[ks % ZP][hf] = a.Wout[(ks * 16 + wave * HF + hf) * 64 + lane];
+  };
+#pragma unroll
+  for (int ks = 0; ks < ZP; ++ks) loadz(ks);
+  put_y(a.k);
+  __syncthreads();
+  f32x4 z[HF][NFC];
+#pragma unroll
+  for (int hf = 0; hf < HF; ++hf)
+#pragma unroll
+    for (int nf = 0; nf < NFC; ++nf) z[hf][nf] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int ks = 0; ks < KD; ++ks) {
+    uint4 bb[NFC];
+#pragma unroll
+    for (int nf = 0; nf < NFC; ++nf) bb[nf] = *(const uint4*)(yrow + nf * 16 * YSTR + ks * 64);
+#pragma unroll
+    for (int hf = 0; hf < HF; ++hf)
+#pragma unroll
+      for (int nf = 0; nf < NFC; ++nf) M::run(z[hf][nf], wz[ks % ZP][hf], bb[nf]);
+    if (ks + ZP < KD) loadz(ks + ZP);
+  }
+#pragma unroll
+  for (int hf = 0; hf < HF; ++hf) {
+    const int v = (wave * HF + hf) * 16 + 4 * lg;
+    const float4 bo = *reinterpret_cast<const float4*>(a.bout + v);
+#pragma unroll
+    for (int nf = 0; nf < NFC; ++nf) {
+      const int m = nf * 16 + lc;
+      const int64_t n = tile0 + m;
+      const float4 zz =
+          make_float4(z[hf][nf][0] + bo.x, z[hf][nf][1] + bo.y, z[hf][nf][2] + bo.z, z[hf][nf][3] + bo.w);
+      *reinterpret_cast<float4*>(Zs + m * ZSTR + v) = zz;
+      if (n < N) {
+        if (a.logits) *reinterpret_cast<float4*>(a.logits + (a.w.n0 + n) * 256 + v) = zz;
+        if (KEEP) *reinterpret_cast<float4*>(a.kZ + n * 256 + v) = zz;
+      }
+    }
+  }
+  __syncthreads();
+  // thread (window m, p): the 16 logits that lane group p % 4 of feature wave
+  // p / 4 holds in k_ffn_head
+  for (int q = tid; q < MB * 16; q += NT) {
+    const int m = q >> 4, p = q & 15;
+    const float* zr = Zs + m * ZSTR + (p >> 2) * 64 + (p & 3) * 4;
+    float x[16];
+#pragma unroll
+    for (int rf = 0; rf < 4; ++rf) {
+      const float4 v = *reinterpret_cast<const float4*>(zr + rf * 16);
+      x[4 * rf] = v.x;
+      x[4 * rf + 1] = v.y;
+      x[4 * rf + 2] = v.z;
+      x[4 * rf + 3] = v.w;
+    }
+    float mx = x[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) mx = fmaxf(mx, x[i]);
+    mx = wave_max16(mx);
+    const float mxl = -mx * TRACE_LOG2E;
+    float se = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) se += __builtin_amdgcn_exp2f(fmaf(x[i], TRACE_LOG2E, mxl));
+    se += __shfl_xor(se, 1, 64);
+    se += __shfl_xor(se, 2, 64);
+    const int b = lane & 48;
+    const float s0 = __shfl(se, b, 64), s1 = __shfl(se, b + 4, 64), s2 = __shfl(se, b + 8, 64),
+                s3 = __shfl(se, b + 12, 64);
+    const int64_t n = tile0 + m;
+    if (p == 0 && n < N)
+      a.bits[a.w.n0 + n] = log2f(((s0 + s1) + s2) + s3) - (Zs[m * ZSTR + tg[m]] - mx) * TRACE_LOG2E;
+  }
+}
+
 // ------------------------------------------------- pipelined bf16 variant ----
 // Same arithmetic as k_ffn_head (bf16 operands, fp32 accumulation, U rounded
 // to bf16 after GELU; the GELU by the exp2 form gelu2_ex), restructured so that
@@ -644,6 +866,15 @@ static void launch_pipe(const FfnArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((k_ffn_pipe<D, MB, false, WC>), grid, dim3(512), 0, s, a);
 }
 
+template <int D, int NFC>
+static void launch_lat(const FfnArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)((a.w.N + 16 * NFC - 1) / (16 * NFC))), block(D >= 128 ? 512 : 256);
+  if (a.kY)
+    hipLaunchKernelGGL((k_ffn_lat<D, NFC, true>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((k_ffn_lat<D, NFC, false>), grid, block, 0, s, a);
+}
+
 template <bool BF, int D>
 static void run_ffn(const FfnArgs& a, hipStream_t s) {
   if constexpr (BF) {
@@ -663,6 +894,14 @@ static void run_ffn(const FfnArgs& a, hipStream_t s) {
   } else {
     constexpr int MB = pick_mb(BF, D), FC = pick_fc(BF, D);
     static_assert(ffn_lds_bytes(BF, D, MB, FC) <= 160 * 1024, "LDS");
+    // launches that give some CUs no MB-window tile: 16 windows per workgroup
+    // while that is at most one workgroup per CU, then 32.  d = 128, F = 512 (us,
+    // wide tiles / these): 4096 windows 157 / 34 (16), 8192 157 / 61 (16, two per
+    // CU), 12288 157 / 94 (32), 16384 157 / 96 (32), 32768 164 / 180 (32)
+    if constexpr (D <= 256) {
+      if (a.w.N <= (int64_t)256 * 16) return launch_lat<D, 1>(a, s);
+      if (a.w.N < (int64_t)256 * MB) return launch_lat<D, 2>(a, s);
+    }
     const dim3 grid((unsigned)((a.w.N + MB - 1) / MB));
     if (a.kY)
       hipLaunchKernelGGL((k_ffn_head<BF, D, MB, FC, true>), grid, dim3(512), 0, s, a);
