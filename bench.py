@@ -187,16 +187,16 @@ def measure_forward(wid, steps_per_call, calls):
 
 
 def attn_kernel(w, steps_per_call):
-    """The attention kernel of a forward launch: bf16 launches of whole
-    64-window tiles per stream share the byte groups between windows, one
-    head per wave at d = 256 with 8 heads and g = 8 (k_attn_wh), one window
-    class per wave otherwise (k_attn_grp); the per-token kernel (k_attn) for
-    the rest."""
-    if w.dtype != "bf16" or steps_per_call % 64:
+    """The attention kernel of a bf16 forward launch: one that shares the byte
+    groups between the windows of 64-position tiles, by head (k_attn_wh) at
+    d >= 128 where a stream's positions fill the tiles, or by alignment class
+    (k_attn_grp) for whole tiles at d = 64; else the per-token kernel (k_attn)."""
+    if w.dtype != "bf16" or w.g not in (4, 8):
         return "k_attn"
-    if w.d == 256 and w.H == 8 and w.g == 8 and w.T in (4, 8):
-        return "k_attn_wh"
-    return "k_attn_grp"
+    if w.d >= 128 and (w.d, w.d // w.H) != (128, 64):
+        tiles, rows = -(-steps_per_call // 64), (64 + w.W - w.g + 15) // 16 * 16
+        return "k_attn_wh" if steps_per_call * (w.T + 1) >= tiles * (rows + 64) else "k_attn"
+    return "k_attn" if steps_per_call % 64 else "k_attn_grp"
 
 
 def traffic_for(kernel, windows_per_launch):

@@ -57,6 +57,9 @@ typedef void (*ffn_fn)(const FfnArgs&, hipStream_t);
 
 // NULL when no kernel is built for the shape.
 attn_fn find_attn(bool bf, int T, int D, int DH);
+// attn_wh.hip: bf16, byte groups shared between the windows of 64-position tiles
+// of each stream; false when the shape is not built
+bool launch_attn_wh(int T, int D, int DH, const AttnArgs& a, hipStream_t s);
 ffn_fn find_ffn(bool bf, int D);
 
 void launch_zero(void* p, int64_t n32, hipStream_t s);
