@@ -30,8 +30,9 @@ struct trace_model {
   float* PW;  // [3][T][D] positional parts of the q, k, v projections
   uint4 *Wq, *Wk, *Wv, *Wo, *W1, *W2, *Wout;
   uint4 *WkT, *WvT;  // bf16 models that keep activations: packed Wk^T, Wv^T (input gradient of the tokens)
-  // bf16 models that keep activations: the master's Wq .. Wout range as bf16
-  // operand values, same order (B operands of the update's products)
+  uint4 *WoT, *W1T, *W2T, *WoutT;  // models that keep activations: packed transposes (the chain of input gradients)
+  // bf16 models that keep activations: the master's Wq, Wk, Wv as bf16 operand
+  // values, same order (B operands of the update's products)
   uint16_t* Wh;
   // Performer attention: packed random projection (device), features, set yet
   uint4* Om;
@@ -55,11 +56,12 @@ struct trace_model {
   float *kq, *kK, *kV, *kA, *kO, *kY, *kU, *kZ;
   uint16_t* kG;  // bf16 models: GELU(U) of each repeat as bf16 operand values
   // backward scratch
-  // dY: gradients w.r.t. the k+1 residual states, dU: w.r.t. the k pre-GELU
-  // activations (one buffer per repeat, read by the weight gradients later);
-  // in bf16 models dU, Xk (the byte-embedding part of the kept tokens) and the
-  // kept Y hold bf16 elements: all are only read as bf16 operands
-  float *dz, *dY, *dU, *G, *dO, *dQ, *dK, *dV, *dX, *Xk, *sP, *gws, *cws, *ews, *apart;
+  // dY0: gradient w.r.t. the FFN's input, dYr: w.r.t. the residual states after
+  // each repeat, dU: w.r.t. the k pre-GELU activations, G: GELU of those (fp32
+  // models), one block per repeat, read by the weight gradients;
+  // in bf16 models dYr, dU, Xk (the byte-embedding part of the kept tokens) and
+  // the kept Y hold bf16 elements: all are only read as bf16 operands
+  float *dz, *dY0, *dYr, *dU, *G, *dO, *dQ, *dK, *dV, *dX, *Xk, *sP, *gws, *cws, *ews, *apart;
   float* dSc;  // [N][H][T] gradients of the last row's attention scores
   int64_t gws_cap;
   // second stream of the update step (the weight-gradient branch), its own
@@ -254,13 +256,18 @@ bool refresh_operands(trace_model* m, hipStream_t s) {
       job(RJ_CVT, th + L.off[P_E], m->Ec, L.size[P_E], 0),
       pos ? job(RJ_CVT, th + L.off[P_P], m->Pc, L.size[P_P], 0)
           : job(RJ_ZERO, nullptr, m->Pc, (L.size[P_P] * (m->bf ? 2 : 4) + 3) / 4, 0),
-      // the update's input gradient of the tokens and the B operands of its
-      // products (bf16 models that keep activations)
+      // models that keep activations: the update's chain of input gradients ([N][K]
+      // sources: a weight of the forward, [K][N] row-major, read as its transpose)
+      job(RJ_PACKT, th + L.at(P_WO, top), m->WoT, D, D),
+      job(RJ_PACKT, th + L.at(P_W1, top), m->W1T, F, D),
+      job(RJ_PACKT, th + L.at(P_W2, top), m->W2T, D, F),
+      job(RJ_PACKT, th + L.off[P_WOUT], m->WoutT, 256, D),
+      // bf16 ones: its input gradient of the tokens and the B operands of its products
       job(RJ_PACKT, th + L.at(P_WK, top), m->WkT, D, D),
       job(RJ_PACKT, th + L.at(P_WV, top), m->WvT, D, D),
-      job(RJ_CVT8, th + L.off[P_WQ], m->Wh, L.off[P_BOUT] - L.off[P_WQ], 0),
+      job(RJ_CVT8, th + L.off[P_WQ], m->Wh, L.off[P_WO] - L.off[P_WQ], 0),
   };
-  const int njobs = (int)(sizeof(jobs) / sizeof(jobs[0])) - (m->WkT ? 0 : 3);
+  const int njobs = (int)(sizeof(jobs) / sizeof(jobs[0])) - (m->WoT ? 0 : 4) - (m->WkT ? 0 : 3);
   bool ok = launch_refresh(m->bf, jobs, njobs, s);
   // untied FFN: the packed copies of repeats 1 .. k-1
   const int64_t es_ = m->bf ? 2 : 4;
@@ -268,8 +275,10 @@ bool refresh_operands(trace_model* m, hipStream_t s) {
     const RefreshJob more[] = {
         job(RJ_PACK, th + L.at(P_W1, top) + (int64_t)r * D * F, (char*)m->W1 + (int64_t)r * D * F * es_, D, F),
         job(RJ_PACK, th + L.at(P_W2, top) + (int64_t)r * F * D, (char*)m->W2 + (int64_t)r * F * D * es_, F, D,
-            m->bf ? 0.5f : 1.f)};
-    ok = launch_refresh(m->bf, more, 2, s);
+            m->bf ? 0.5f : 1.f),
+        job(RJ_PACKT, th + L.at(P_W1, top) + (int64_t)r * D * F, (char*)m->W1T + (int64_t)r * D * F * es_, F, D),
+        job(RJ_PACKT, th + L.at(P_W2, top) + (int64_t)r * F * D, (char*)m->W2T + (int64_t)r * F * D * es_, D, F)};
+    ok = launch_refresh(m->bf, more, m->WoT ? 4 : 2, s);
   }
   tend(m, tk, TRACE_KIND_REFRESH, s);
   return ok;
@@ -504,15 +513,18 @@ extern "C" int trace_create(const trace_config* cfg, trace_model** out) {
          dalloc(m, &m->kY, (cfg->k + 1) * K * D * es) && dalloc(m, &m->kU, cfg->k * K * F * 4) &&
          (!bf || dalloc(m, &m->kG, cfg->k * K * F * 2)) &&
          dalloc(m, &m->kZ, K * 256 * 4) && dalloc(m, &m->dz, K * 256 * 4) &&
-         dalloc(m, &m->dY, (cfg->k + 1) * K * D * 4) && dalloc(m, &m->dU, cfg->k * K * F * es) &&
-         (bf || dalloc(m, &m->G, K * F * 4)) &&
+         dalloc(m, &m->dY0, K * D * 4) && dalloc(m, &m->dYr, cfg->k * K * D * es) &&
+         dalloc(m, &m->dU, cfg->k * K * F * es) && (bf || dalloc(m, &m->G, cfg->k * K * F * 4)) &&
+         dalloc(m, &m->WoT, D * D * es) && dalloc(m, &m->WoutT, 256 * D * es) &&
+         dalloc(m, &m->W1T, D * F * es * (cfg->untied_ffn ? cfg->k : 1)) &&
+         dalloc(m, &m->W2T, D * F * es * (cfg->untied_ffn ? cfg->k : 1)) &&
          dalloc(m, &m->dO, K * D * 4) && dalloc(m, &m->dQ, K * D * 4) && dalloc(m, &m->dK, K * T * D * 4) &&
          dalloc(m, &m->dV, K * T * D * 4) && dalloc(m, &m->dX, K * T * D * 4) && dalloc(m, &m->Xk, K * T * D * es) &&
          dalloc(m, &m->sP, (2 * T + 2) * D * 4) &&
          dalloc(m, &m->apart, std::max(attn_bwd_part_floats(K, T, D, cfg->H), rank1_sums_part_floats(K, T, D)) * 4) &&
          dalloc(m, &m->dSc, K * cfg->H * T * 4) &&
          (!bf || (dalloc(m, &m->WkT, (int64_t)D * D * 2) && dalloc(m, &m->WvT, (int64_t)D * D * 2) &&
-                  dalloc(m, &m->Wh, (m->L.off[P_BOUT] - m->L.off[P_WQ]) * 2))) &&
+                  dalloc(m, &m->Wh, (m->L.off[P_WO] - m->L.off[P_WQ]) * 2))) &&
          dalloc(m, &m->gws, (m->gws_cap = adapt_gemm_ws(m, K)) * 4) &&
          dalloc(m, &m->ews, embed_bwd_ws_floats(K * W, cfg->e) * 4) &&
          dalloc(m, &m->cws, colsum_ws_floats(std::max<int64_t>((int64_t)(2 * T + 2) * D, 256)) * 4) &&
@@ -780,14 +792,14 @@ extern "C" int trace_adapt_step(trace_model* m, void* stream) {
   bool ok = true;  // false if a product could not be launched
   // Two streams: s carries the chain of input gradients (dY, dU, dO, dQ/dK/dV,
   // dX, dE) and never waits for the other until the end; `side` computes the
-  // weight gradients from the per-repeat buffers that chain leaves behind, each
+  // weight gradients from the buffers that chain leaves behind, each
   // as soon as its operands exist (a wait across streams costs several
   // microseconds, so only the side stream waits).  The side stream has its own
   // split-K and column-sum workspaces of the same sizes, so every product is the
   // same as on one stream.
   // Buffers by writer -> readers (every cross-stream read follows a mark of the
   // writer's stream, or, for the side stream's results, the final wait of s):
-  //   s: dz -> s, side; dY_r, dU_r -> s, side (one buffer per repeat); dO, dX,
+  //   s: dz, dY_r, dU_r (one block per repeat), G, dO -> s, side; dX,
   //      grad P, grad E -> s; dQ, dK, dV -> s, side
   //   s: sums over windows in sP (dK, dV, dQ before the mark that the side
   //      stream waits on; dY_0 after it, read by s only)
@@ -796,12 +808,12 @@ extern "C" int trace_adapt_step(trace_model* m, void* stream) {
   //   so the next forward cannot overwrite them while side still reads
   const hipStream_t w = m->side;
   float* ws2 = m->gws2;
-  auto dYr = [&](int r) { return m->dY + (int64_t)r * N * D; };  // w.r.t. the input of repeat r (r = k: Y_k)
-  const int hf = m->bf ? 1 : 0;  // dU, Xk, kY stored as bf16
+  const int hf = m->bf ? 1 : 0;  // dY_r (r > 0), dU, Xk, kY stored as bf16
   // bf16 element e of a buffer whose elements are bf16 (hf) or fp32
   auto at = [&](float* p, int64_t e) { return hf ? (float*)((uint16_t*)p + e) : p + e; };
+  auto dYr = [&](int r) { return at(m->dYr, (int64_t)(r - 1) * N * D); };  // w.r.t. the output of repeat r - 1, r > 0
   auto dUr = [&](int r) { return at(m->dU, (int64_t)r * N * F); };
-  // B operand from a weight of the master at offset o (Wq .. Wout): its bf16
+  // B operand from a weight of the master at offset o (Wq .. Wv): its bf16
   // image when the model keeps one (the same rounded values, half the bytes)
   const int hw = m->Wh ? 1 : 0;
   auto wsrc = [&](int64_t o) {
@@ -812,8 +824,28 @@ extern "C" int trace_adapt_step(trace_model* m, void* stream) {
   // lower_backward runs each lower layer down to the tokens
   const int NL = L.NL, top = NL - 1;
   const float* Xtop = NL > 1 ? m->klX + (int64_t)top * m->max_keep * T * D : nullptr;
-  // head: dz = (softmax(z) - onehot) / N
-  launch_ce_grad(m->kZ, m->ktgt, N, m->dz, s);
+  // dz, dY_k .. dY_0, dU_r and dO in one launch
+  ChainArgs ca;
+  ca.N = N;
+  ca.F = F;
+  ca.k = k;
+  ca.wstride = m->cfg.untied_ffn ? (int64_t)D * F * (m->bf ? 2 : 4) / 16 : 0;
+  ca.z = m->kZ;
+  ca.tgt = m->ktgt;
+  ca.kU = m->kU;
+  ca.WoutT = m->WoutT;
+  ca.W2T = m->W2T;
+  ca.W1T = m->W1T;
+  ca.WoT = m->WoT;
+  ca.dz = m->dz;
+  ca.dYr = m->dYr;
+  ca.dY0 = m->dY0;
+  ca.dU = m->dU;
+  ca.G = m->G;
+  ca.dO = m->dO;
+  ok = launch_bwd_chain(m->bf, D, ca, s) && ok;
+  // the side stream starts once dO is done: its large products share the CUs with
+  // the attention backward's memory-bound kernels
   order(m, s, w);
   // bf16 models: the key and value gradients are used through their rank-one
   // rows dK_h[n][t] = dS[n][h][t] scale q_h[n], dV_h[n][t] = A[n][h][t] bf(dO_h[n])
@@ -835,72 +867,26 @@ extern "C" int trace_adapt_step(trace_model* m, void* stream) {
   go.halfA = hf;
   ok = launch_gemm(go, ws2, m->gws_cap, w) && ok;
   launch_colsum(m->dz, N, 256, 256, gr + L.off[P_BOUT], 0.f, m->cws2, w);
-  // dY_k = dz . Wout^T
-  GemmArgs gk = gemm(N, D, 256, m->dz, 256, 1, rb, wsrc(L.off[P_WOUT]), 1, 256, rb, dYr(k), D, 0.f);
-  gk.halfB = hw;
-  ok = launch_gemm(gk, ws, m->gws_cap, s) && ok;
-  // shared FFN, repeats in reverse: dU_r = (dY_{r+1} . W2^T) * GELU'(U_r),
-  // dY_r = dY_{r+1} + dU_r . W1^T; once dU_r exists the side stream forms
-  // dW2 += G_r^T . dY_{r+1} and dW1 += Y_r^T . dU_r (accumulated over the repeats
-  // in reverse; G = GELU(U) at its storage point: kept by the bf16 forward,
-  // formed here otherwise).  With shared weights and G kept, the sums over the
-  // repeats are single products over k N rows instead (the per-repeat buffers
-  // are consecutive: G_0..G_{k-1} with dY_1..dY_k, Y_0..Y_{k-1} with dU_0..dU_{k-1}),
-  // formed on the side stream once dO is done (below).
-  const bool merged = m->kG && !m->cfg.untied_ffn;
-  for (int r = k - 1; r >= 0; --r) {
-    // untied FFN: repeat r's own W1, W2 and gradient blocks (each written once)
-    const int64_t wr = m->cfg.untied_ffn ? (int64_t)r * D * F : 0;
-    GemmArgs gd = gemm(N, F, D, dYr(r + 1), D, 1, rb, wsrc(L.at(P_W2, top) + wr), 1, D, rb, dUr(r), F, 0.f);
-    gd.gelu_u = m->kU + (int64_t)r * N * F;
-    gd.halfC = hf;
-    gd.halfB = hw;
-    ok = launch_gemm(gd, ws, m->gws_cap, s) && ok;
-    if (!merged) {
-      order(m, s, w);  // dY_{r+1} and dU_r are complete
-      const float beta = (r == k - 1 || m->cfg.untied_ffn) ? 0.f : 1.f;
-      GemmArgs g2w;
-      if (m->kG) {
-        g2w = gemm(F, D, N, (const float*)(m->kG + (int64_t)r * N * F), 1, F, rb, dYr(r + 1), D, 1, rb,
-                   gr + L.at(P_W2, top) + wr, D, beta);
-        g2w.halfA = 1;
-      } else {
-        launch_gelu_fwd_round(m->kU + (int64_t)r * N * F, m->G, (int64_t)N * F, rb, w);
-        g2w = gemm(F, D, N, m->G, 1, F, rb, dYr(r + 1), D, 1, rb, gr + L.at(P_W2, top) + wr, D, beta);
-      }
-      ok = launch_gemm(g2w, ws2, m->gws_cap, w) && ok;
-      GemmArgs g1w =
-          gemm(D, F, N, at(m->kY, (int64_t)r * N * D), 1, D, rb, dUr(r), F, 1, rb, gr + L.at(P_W1, top) + wr, F, beta);
-      g1w.halfA = g1w.halfB = hf;
-      ok = launch_gemm(g1w, ws2, m->gws_cap, w) && ok;
-    }
-    // dY_r = dY_{r+1} + dU_r . W1^T (the addend read from dY_{r+1}'s own buffer)
-    GemmArgs gy = gemm(N, D, F, dUr(r), F, 1, rb, wsrc(L.at(P_W1, top) + wr), 1, F, rb, dYr(r), D, 1.f);
-    gy.Cin = dYr(r + 1);
-    gy.halfA = hf;
-    gy.halfB = hw;
-    ok = launch_gemm(gy, ws, m->gws_cap, s) && ok;
-  }
-  // attention output projection: dO = dY_0 . Wo^T, then the attention (last
-  // query row) -> dQ, dK, dV
-  GemmArgs go2 = gemm(N, D, D, dYr(0), D, 1, rb, wsrc(L.at(P_WO, top)), 1, D, rb, m->dO, D, 0.f);
-  go2.halfB = hw;
-  ok = launch_gemm(go2, ws, m->gws_cap, s) && ok;
-  // the side stream's large products start once dO is done (dY_0 complete), so
-  // that they share the CUs with the attention backward's memory-bound kernels
-  // rather than with the FFN chain's products
-  order(m, s, w);
-  if (merged) {
-    // dW2 = sum_r G_r^T dY_{r+1} and dW1 = sum_r Y_r^T dU_r over the k N rows
-    GemmArgs g2w = gemm(F, D, k * N, (const float*)m->kG, 1, F, rb, dYr(1), D, 1, rb, gr + L.at(P_W2, top), D, 0.f);
-    g2w.halfA = 1;
+  // side: dW2 = sum_r G_r^T dY_{r+1}, dW1 = sum_r Y_r^T dU_r (G = GELU(U) at its
+  // storage point: kept by the bf16 forward, left by the chain otherwise).  With
+  // shared weights the sums over the repeats are single products over k N rows (the
+  // per-repeat blocks are consecutive: G_0..G_{k-1} with dY_1..dY_k, Y_0..Y_{k-1}
+  // with dU_0..dU_{k-1}).
+  float* Gk = m->bf ? (float*)m->kG : m->G;
+  const int np = m->cfg.untied_ffn ? k : 1, rows = m->cfg.untied_ffn ? N : k * N;
+  for (int r = 0; r < np; ++r) {
+    const int64_t wr = (int64_t)r * D * F;
+    GemmArgs g2w = gemm(F, D, rows, at(Gk, (int64_t)r * N * F), 1, F, rb, dYr(r + 1), D, 1, rb,
+                        gr + L.at(P_W2, top) + wr, D, 0.f);
+    g2w.halfA = g2w.halfB = hf;
     ok = launch_gemm(g2w, ws2, m->gws_cap, w) && ok;
-    GemmArgs g1w = gemm(D, F, k * N, m->kY, 1, D, rb, m->dU, F, 1, rb, gr + L.at(P_W1, top), F, 0.f);
+    GemmArgs g1w = gemm(D, F, rows, at(m->kY, (int64_t)r * N * D), 1, D, rb, dUr(r), F, 1, rb,
+                        gr + L.at(P_W1, top) + wr, F, 0.f);
     g1w.halfA = g1w.halfB = hf;
     ok = launch_gemm(g1w, ws2, m->gws_cap, w) && ok;
   }
   // side: dWo = O^T . dY_0
-  launch_gemm(gemm(D, D, N, m->kO, 1, D, rb, dYr(0), D, 1, rb, gr + L.at(P_WO, top), D, 0.f), ws2, m->gws_cap, w);
+  launch_gemm(gemm(D, D, N, m->kO, 1, D, rb, m->dY0, D, 1, rb, gr + L.at(P_WO, top), D, 0.f), ws2, m->gws_cap, w);
   // sP: [0, T D) sum over windows of dK, [T D, 2T D) of dV (from the attention
   // backward), [2T D, (2T+1) D) of dQ, [(2T+1) D, (2T+2) D) of dY_0
   float* sK = m->sP;
@@ -915,7 +901,7 @@ extern "C" int trace_adapt_step(trace_model* m, void* stream) {
   launch_attn_bwd(m->dO, m->kq, m->kK, m->kV, m->kA, N, T, D, H, ascale, rb, m->dQ, rank1 ? nullptr : m->dK,
                   rank1 ? nullptr : m->dV, rank1 ? nullptr : m->apart, sK, m->cws, s, m->bf ? m->dSc : nullptr);
   if (sums1 &&
-      !launch_rank1_sums(m->dSc, m->kq, m->kA, m->dO, m->dQ, dYr(0), N, T, D, H, ascale, rb, m->apart, sK, m->cws, s))
+      !launch_rank1_sums(m->dSc, m->kq, m->kA, m->dO, m->dQ, m->dY0, N, T, D, H, ascale, rb, m->apart, sK, m->cws, s))
     ok = false;
   auto log2i = [](int x) {
     int r = 0;
@@ -980,7 +966,7 @@ extern "C" int trace_adapt_step(trace_model* m, void* stream) {
   // form the key and value part from the rank-one rows of dK and dV
   // (launch_dx_rank1, which adds dY_0); otherwise two products over every token
   // row, then dY_0
-  if (rank1) ok = launch_dx_rank1(m->kq, m->dO, m->dSc, m->kA, m->WkT, m->WvT, dYr(0), N, T, D, H, ascale, m->dX, s) && ok;
+  if (rank1) ok = launch_dx_rank1(m->kq, m->dO, m->dSc, m->kA, m->WkT, m->WvT, m->dY0, N, T, D, H, ascale, m->dX, s) && ok;
   if (!rank1) {
     GemmArgs gxk = gemm(N * T, D, D, m->dK, D, 1, 0, wsrc(L.at(P_WK, top)), 1, D, rb, m->dX, D, 0.f);
     GemmArgs gxv = gemm(N * T, D, D, m->dV, D, 1, 0, wsrc(L.at(P_WV, top)), 1, D, rb, m->dX, D, 0.f);
@@ -991,7 +977,7 @@ extern "C" int trace_adapt_step(trace_model* m, void* stream) {
                       (int64_t)T * D, 1.f);
   gxq.halfB = hw;
   ok = launch_gemm(gxq, ws, m->gws_cap, s) && ok;
-  if (!rank1) launch_add(m->dX + (int64_t)(T - 1) * D, dYr(0), N, D, (int64_t)T * D, D, s);
+  if (!rank1) launch_add(m->dX + (int64_t)(T - 1) * D, m->dY0, N, D, (int64_t)T * D, D, s);
   if (NL > 1) {
     // dX is the gradient w.r.t. the top layer's input: down through the lower
     // layers (on this stream, after the side stream's work: layer 0 reads Xk)
@@ -1004,7 +990,7 @@ extern "C" int trace_adapt_step(trace_model* m, void* stream) {
   } else if (m->cfg.use_pos) {
     // positional table: dP[t] = sum_n dX[n][t], from the sums over windows of
     // dK, dV, dQ and dY_0 times the weights; then the byte embedding
-    if (!sums1) launch_colsum(dYr(0), N, D, D, sY, 0.f, m->cws, s);
+    if (!sums1) launch_colsum(m->dY0, N, D, D, sY, 0.f, m->cws, s);
     launch_pos_table_grad(sK, sQ, sY, th + L.at(P_WQ, top), th + L.at(P_WK, top), th + L.at(P_WV, top), T, D, rb,
                           gr + L.off[P_P], s);
   } else {

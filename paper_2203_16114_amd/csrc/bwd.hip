@@ -534,39 +534,6 @@ void launch_colsum(const float* in, int64_t rows, int64_t cols, int64_t ld, floa
   hipLaunchKernelGGL(k_colsum2, dim3((unsigned)((cols + 63) / 64)), dim3(256), 0, s, ws, cols, out, beta);
 }
 
-// ------------------------------------------------------ head: dz of the CE ----
-// dz[n] = (softmax(z[n]) - onehot(y[n])) / N for the mean cross-entropy in nats.
-// One wave per window; each lane holds 4 of the 256 logits.
-__global__ __launch_bounds__(256) void k_ce_grad(const float* __restrict__ z, const int32_t* __restrict__ tgt, int64_t N,
-                                                 float* __restrict__ dz) {
-  const int lane = threadIdx.x & 63;
-  const int64_t n = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (n >= N) return;
-  float v[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = z[n * 256 + lane + 64 * i];
-  float mx = fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3]));
-  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-  float ex[4], sm = 0.f;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    ex[i] = expf(v[i] - mx);
-    sm += ex[i];
-  }
-  for (int o = 32; o > 0; o >>= 1) sm += __shfl_xor(sm, o, 64);
-  const int y = tgt[n];
-  const float fn = (float)N;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c = lane + 64 * i;
-    const float p = ex[i] / sm;
-    dz[n * 256 + c] = (p - (c == y ? 1.f : 0.f)) / fn;
-  }
-}
-void launch_ce_grad(const float* z, const int32_t* tgt, int64_t N, float* dz, hipStream_t s) {
-  hipLaunchKernelGGL(k_ce_grad, dim3((unsigned)((N + 3) / 4)), dim3(256), 0, s, z, tgt, N, dz);
-}
-
 // -------------------------------------------------------------- elementwise ----
 __global__ void k_gelu_fwd_round(const float* __restrict__ U, float* __restrict__ G, int64_t n, int round) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;

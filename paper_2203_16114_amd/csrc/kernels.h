@@ -81,7 +81,7 @@ struct RefreshJob {
   int kind, K, N, use_pos;
   float scale;
 };
-constexpr int REFRESH_MAX_JOBS = 13;
+constexpr int REFRESH_MAX_JOBS = 17;
 // Runs jobs[0..n) on stream s; false (nothing launched) for an unsupported job.
 bool launch_refresh(bool bf, const RefreshJob* jobs, int n, hipStream_t s);
 
@@ -138,10 +138,28 @@ int64_t bgemm_ws_floats(int M, int N, int K);
 // product is not one it takes
 bool launch_fgemm(const GemmArgs& g, const GemmArgs* g2, float* ws, int64_t ws_cap, hipStream_t s);
 
+// bchain.hip: the input gradients from the kept logits down to dO in one launch
+struct ChainArgs {
+  int64_t N;
+  int F, k;
+  int64_t wstride;                         // uint4 between the packed W1^T (W2^T) copies of two repeats; 0: shared
+  const float* z;                          // [N][256] kept logits
+  const int32_t* tgt;                      // [N]
+  const float* kU;                         // [k][N][F] kept pre-GELU activations
+  const uint4 *WoutT, *W2T, *W1T, *WoT;    // fragment-packed operand copies of the transposes (RJ_PACKT)
+  float* dz;                               // [N][256]
+  void* dYr;                               // [k][N][D]: dY_1 .. dY_k as operand values (bf16 or fp32)
+  float* dY0;                              // [N][D]
+  void* dU;                                // [k][N][F] operand values
+  float* G;                                // fp32 models: [k][N][F] GELU(U)
+  float* dO;                               // [N][D]
+};
+// false when the shape is not built
+bool launch_bwd_chain(bool bf, int D, const ChainArgs& a, hipStream_t s);
+
 void launch_colsum(const float* in, int64_t rows, int64_t cols, int64_t ld, float* out, float beta, float* ws,
                    hipStream_t s);
 int64_t colsum_ws_floats(int64_t cols);
-void launch_ce_grad(const float* z, const int32_t* tgt, int64_t N, float* dz, hipStream_t s);
 void launch_gelu_fwd_round(const float* U, float* G, int64_t n, int round, hipStream_t s);
 void launch_gelu_bwd(const float* dG, const float* U, float* dU, int64_t n, hipStream_t s);
 // dS (nullable): [N][H][T] gradients of the attention scores of the last row
