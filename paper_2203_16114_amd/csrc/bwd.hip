@@ -9,6 +9,8 @@
 
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 // ------------------------------------------------------------ generic GEMM ----
 // C(m,n) [+]= sum_k A(m,k) B(k,n) for arbitrary element strides.  64x64 output
 // tile per workgroup, 4 waves in a 2x2 layout of 32x32 sub-tiles; the k range
@@ -1581,6 +1583,8 @@ void launch_pos_table_grad(const float* sKV, const float* sQ, const float* sY, c
 // order by one wave (k_emb_piece); the pieces of a byte are added in a fixed
 // order (k_emb_sum).
 // The order of every sum depends on the input bytes alone.
+constexpr int EMB_SLICE = 16384;                 // positions per slice of the sliced sums
+constexpr int64_t EMB_SLICED = (int64_t)1 << 18;  // largest batch that takes them
 constexpr int EMB_CS = 2048;    // positions per block of the counting sort
 constexpr int EMB_PIECE = 256;  // positions per piece
 
@@ -1605,7 +1609,9 @@ static EmbWs emb_ws(float* ws, int64_t M, int e) {
 }
 int64_t embed_bwd_ws_floats(int64_t M, int e) {
   const int64_t nb = (M + EMB_CS - 1) / EMB_CS, pmax = (M + EMB_PIECE - 1) / EMB_PIECE + 256;
-  return 2 * nb * 256 + 512 + 260 + 3 * pmax + M + 3 + pmax * e;
+  const int64_t sorted = 2 * nb * 256 + 512 + 260 + 3 * pmax + M + 3 + pmax * e;
+  const int64_t sliced = (std::min(M, EMB_SLICED) + EMB_SLICE - 1) / EMB_SLICE * 256 * e;
+  return std::max(sorted, sliced);
 }
 
 // cnt[b][v] = number of positions of block b (EMB_CS positions) holding byte v
@@ -1821,11 +1827,143 @@ __global__ __launch_bounds__(256) void k_emb_sum(const float* __restrict__ part,
   }
 }
 
+// The same sums for batches up to EMB_SLICED positions, in one launch (two when
+// there are several slices): block (v, slice) lists the slice's positions that hold
+// byte v, in order, from the 16 KiB of window bytes themselves (every byte value's
+// block reads them, from L2), and sums their dX rows: row i of the list goes to
+// thread group i % RP (groups of 4-float lanes, one row each, eight rows in flight
+// per lane), the groups of a wave are added in a fixed tree and the waves in order.
+// The counting sort above takes four launches whose kernels last 3-6 us each
+// before the rows are read: at 16384 positions (512 windows of 32 bytes, e = 32)
+// 25 -> 5 us of kernels in one launch instead of six, at 131072 37 -> 17 in two; at
+// 524288 (e = 64) 75 -> 67 alone, but the blocks crowd the other stream's products
+// there (update 1.234 -> 1.268 ms), hence the line.
+__global__ __launch_bounds__(512) void k_emb_sliced(const uint8_t* __restrict__ win, int M, const float* __restrict__ dX,
+                                                    int e, int lsh, float* __restrict__ out) {
+  __shared__ uint16_t list[EMB_SLICE];
+  __shared__ int wsum[8];
+  __shared__ __align__(16) float red[8][128];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int v = blockIdx.x, q0 = blockIdx.y * EMB_SLICE;
+  // this thread's 32 positions: bit 8 b + 7 of hit[w] says whether byte b of word w is v
+  uint32_t hit[8];
+  int n = 0;
+  const uint32_t vv = (uint32_t)v * 0x01010101u;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int q = q0 + tid * 32 + h * 16;
+    uint4 x = make_uint4(~vv, ~vv, ~vv, ~vv);  // no match
+    if (q + 16 <= M) {
+      x = *reinterpret_cast<const uint4*>(win + q);
+    } else if (q < M) {
+      uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (q + i < M) w[i / 4] = (w[i / 4] & ~(0xffu << (8 * (i % 4)))) | ((uint32_t)win[q + i] << (8 * (i % 4)));
+      x = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+    const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t z = w[i] ^ vv;  // a zero byte where it matches
+      hit[4 * h + i] = ~(((z & 0x7f7f7f7fu) + 0x7f7f7f7fu) | z | 0x7f7f7f7fu);
+      n += __popc(hit[4 * h + i]);
+    }
+  }
+  int inc = n;  // inclusive scan over the wave, then over the waves
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(inc, d, 64);
+    if (lane >= d) inc += o;
+  }
+  if (lane == 63) wsum[wave] = inc;
+  __syncthreads();
+  int at = inc - n, total = 0;
+#pragma unroll
+  for (int w = 0; w < 8; ++w) {
+    if (w < wave) at += wsum[w];
+    total += wsum[w];
+  }
+#pragma unroll
+  for (int w = 0; w < 8; ++w) {
+    uint32_t m = hit[w];
+    while (m) {
+      const int b = __ffs(m) - 1;  // 8 byte + 7
+      list[at++] = (uint16_t)(tid * 32 + 4 * w + (b >> 3));
+      m &= m - 1;
+    }
+  }
+  __syncthreads();
+  // rows: 1 << lsh lanes each (4 features a lane; lanes past e add nothing)
+  const int c = (tid & ((1 << lsh) - 1)) * 4, rp = 512 >> lsh, r0 = tid >> lsh;
+  const bool on = c < e;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  constexpr int B = 8;
+  for (int i0 = r0; i0 < total; i0 += B * rp) {
+    float4 x[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int i = min(i0 + u * rp, total - 1);
+      x[u] = *reinterpret_cast<const float4*>(dX + (int64_t)(q0 + list[i]) * e + (on ? c : 0));
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u)
+      if (i0 + u * rp < total) {
+        acc.x += x[u].x;
+        acc.y += x[u].y;
+        acc.z += x[u].z;
+        acc.w += x[u].w;
+      }
+  }
+  for (int d = 1 << lsh; d < 64; d <<= 1) {
+    acc.x += __shfl_xor(acc.x, d, 64);
+    acc.y += __shfl_xor(acc.y, d, 64);
+    acc.z += __shfl_xor(acc.z, d, 64);
+    acc.w += __shfl_xor(acc.w, d, 64);
+  }
+  if (lane < (1 << lsh) && on) *reinterpret_cast<float4*>(&red[wave][c]) = acc;
+  __syncthreads();
+  if (tid < e) {
+    float t = red[0][tid];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) t += red[w][tid];
+    out[((int64_t)blockIdx.y * 256 + v) * e + tid] = t;
+  }
+}
+
+// dE[i] = sum of the slices' part[z][i], z increasing
+__global__ __launch_bounds__(256) void k_emb_slices(const float* __restrict__ part, int slices, int n,
+                                                    float* __restrict__ dE) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  float t = 0.f;
+  int z = 0;
+  for (; z + 8 <= slices; z += 8) {
+    float x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = part[(int64_t)(z + u) * n + i];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t += x[u];
+  }
+  for (; z < slices; ++z) t += part[(int64_t)z * n + i];
+  dE[i] = t;
+}
+
 void launch_embed_bwd(const uint8_t* win, const float* dX, int64_t N, int W, int e, float* dE, float* ws,
                       hipStream_t s) {
   const int64_t M = N * W;
   if (M <= 0) {
     launch_zero(dE, (int64_t)256 * e, s);
+    return;
+  }
+  if (M <= EMB_SLICED && e % 4 == 0 && e <= 128 && ((uintptr_t)win & 15) == 0 && ((uintptr_t)dX & 15) == 0) {
+    const int slices = (int)((M + EMB_SLICE - 1) / EMB_SLICE);
+    int lsh = 0;  // lanes per row: the power of two that holds e / 4
+    while ((4 << lsh) < e) ++lsh;
+    hipLaunchKernelGGL(k_emb_sliced, dim3(256, slices), dim3(512), 0, s, win, (int)M, dX, e, lsh,
+                       slices > 1 ? ws : dE);
+    if (slices > 1)
+      hipLaunchKernelGGL(k_emb_slices, dim3((unsigned)e), dim3(256), 0, s, (const float*)ws, slices, 256 * e, dE);
     return;
   }
   const EmbWs w = emb_ws(ws, M, e);
