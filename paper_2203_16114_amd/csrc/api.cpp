@@ -68,6 +68,7 @@ struct trace_model {
   // split-K and column-sum workspaces, and the events that order the two streams
   hipStream_t side;
   float *gws2, *cws2;
+  int64_t gws2_cap;
   std::vector<hipEvent_t> sev;
   size_t sev_next;
   std::vector<void*> allocs;
@@ -155,6 +156,20 @@ int64_t adapt_gemm_ws(const trace_model* m, int64_t N) {
     w = std::max(w, std::max(gemm_ws_floats(s[0], s[1], s[2]), bgemm_ws_floats(s[0], s[1], s[2])));
   if (m->bf) w = std::max(w, kv_wgrad_ws_floats(N, m->L.T, m->L.D, m->cfg.H));
   return w;
+}
+
+// Floats of the side stream's workspace: the largest product's partial sums, or
+// those of all the weight gradients that wait for their sum together.
+int64_t adapt_group_ws(const trace_model* m, int64_t N) {
+  const int D = m->L.D, F = m->cfg.F, T = m->L.T, n = (int)N, kn = (m->cfg.untied_ffn ? 1 : m->cfg.k) * n;
+  const bool bf = m->bf;
+  int64_t w = wgrad_ws_floats(bf, D, 256, n) + wgrad_ws_floats(bf, F, D, kn) + wgrad_ws_floats(bf, D, F, kn) +
+              2 * wgrad_ws_floats(bf, D, D, n);
+  if (bf)
+    w += std::max(kv_wgrad_ws_floats(N, T, D, m->cfg.H), bgemm_ws_floats(D, D, n * T)) + bgemm_ws_floats(D, D, n);
+  else
+    w += 2 * wgrad_ws_floats(bf, D, D, n * T);
+  return std::max(w, m->gws_cap);
 }
 
 hipStream_t S(void* s) { return (hipStream_t)s; }
@@ -304,6 +319,7 @@ GemmArgs gemm(int M, int N, int K, const float* A, int64_t sam, int64_t sak, int
   g.gelu_u = nullptr;
   g.halfA = g.halfB = g.halfC = 0;
   g.rowwise = 0;
+  g.defer = nullptr;
   g.Cin = nullptr;
   g.r1c = nullptr;
   g.r1tsh = g.r1dsh = g.r1H = g.r1round = 0;
@@ -528,7 +544,7 @@ extern "C" int trace_create(const trace_config* cfg, trace_model** out) {
          dalloc(m, &m->gws, (m->gws_cap = adapt_gemm_ws(m, K)) * 4) &&
          dalloc(m, &m->ews, embed_bwd_ws_floats(K * W, cfg->e) * 4) &&
          dalloc(m, &m->cws, colsum_ws_floats(std::max<int64_t>((int64_t)(2 * T + 2) * D, 256)) * 4) &&
-         dalloc(m, &m->gws2, m->gws_cap * 4) && dalloc(m, &m->cws2, colsum_ws_floats(T * D) * 4);
+         dalloc(m, &m->gws2, (m->gws2_cap = adapt_group_ws(m, K)) * 4) && dalloc(m, &m->cws2, colsum_ws_floats(T * D) * 4);
     if (ok) ok = hipStreamCreateWithFlags(&m->side, hipStreamNonBlocking) == hipSuccess;
     for (int i = 0; ok && i < 16; ++i) {
       hipEvent_t ev;
@@ -807,7 +823,6 @@ extern "C" int trace_adapt_step(trace_model* m, void* stream) {
   //   kept activations (forward, on s) -> both; s waits for side before Adam,
   //   so the next forward cannot overwrite them while side still reads
   const hipStream_t w = m->side;
-  float* ws2 = m->gws2;
   const int hf = m->bf ? 1 : 0;  // dY_r (r > 0), dU, Xk, kY stored as bf16
   // bf16 element e of a buffer whose elements are bf16 (hf) or fp32
   auto at = [&](float* p, int64_t e) { return hf ? (float*)((uint16_t*)p + e) : p + e; };
@@ -862,31 +877,45 @@ extern "C" int trace_adapt_step(trace_model* m, void* stream) {
   const bool xlast = kvfold && launch_gather_last(m->kwin, N, (const uint16_t*)m->Ec, T, D, m->cfg.e, m->cfg.g,
                                                  (uint16_t*)m->Xk, w);
   if (!xlast) launch_gather_kept(m->bf, m->kwin, N, m->Ec, T, D, m->cfg.e, m->cfg.g, m->Xk, w);
-  GemmArgs go =
-      gemm(D, 256, N, at(m->kY, (int64_t)k * N * D), 1, D, rb, m->dz, 256, 1, rb, gr + L.off[P_WOUT], 256, 0.f);
-  go.halfA = hf;
-  ok = launch_gemm(go, ws2, m->gws_cap, w) && ok;
   launch_colsum(m->dz, N, 256, 256, gr + L.off[P_BOUT], 0.f, m->cws2, w);
   // side: dW2 = sum_r G_r^T dY_{r+1}, dW1 = sum_r Y_r^T dU_r (G = GELU(U) at its
   // storage point: kept by the bf16 forward, left by the chain otherwise).  With
   // shared weights the sums over the repeats are single products over k N rows (the
   // per-repeat blocks are consecutive: G_0..G_{k-1} with dY_1..dY_k, Y_0..Y_{k-1}
   // with dU_0..dU_{k-1}).
+  // With dWout = h_k^T . dz and dWo = O^T . dY_0 they go out in one launch, and the
+  // split-K sums of all weight gradients in one at the end.
   float* Gk = m->bf ? (float*)m->kG : m->G;
-  const int np = m->cfg.untied_ffn ? k : 1, rows = m->cfg.untied_ffn ? N : k * N;
-  for (int r = 0; r < np; ++r) {
+  RedJob red[RED_MAX_JOBS];
+  int nred = 0;
+  float* wsx = m->gws2;  // the side stream's workspace past the sums that wait
+  int64_t capx = m->gws2_cap;
+  auto ffn_grads = [&](int r, int rows, GemmArgs* g) {
     const int64_t wr = (int64_t)r * D * F;
-    GemmArgs g2w = gemm(F, D, rows, at(Gk, (int64_t)r * N * F), 1, F, rb, dYr(r + 1), D, 1, rb,
-                        gr + L.at(P_W2, top) + wr, D, 0.f);
-    g2w.halfA = g2w.halfB = hf;
-    ok = launch_gemm(g2w, ws2, m->gws_cap, w) && ok;
-    GemmArgs g1w = gemm(D, F, rows, at(m->kY, (int64_t)r * N * D), 1, D, rb, dUr(r), F, 1, rb,
-                        gr + L.at(P_W1, top) + wr, F, 0.f);
-    g1w.halfA = g1w.halfB = hf;
-    ok = launch_gemm(g1w, ws2, m->gws_cap, w) && ok;
+    g[0] = gemm(F, D, rows, at(Gk, (int64_t)r * N * F), 1, F, rb, dYr(r + 1), D, 1, rb, gr + L.at(P_W2, top) + wr, D, 0.f);
+    g[1] = gemm(D, F, rows, at(m->kY, (int64_t)r * N * D), 1, D, rb, dUr(r), F, 1, rb, gr + L.at(P_W1, top) + wr, F, 0.f);
+    g[0].halfA = g[0].halfB = g[1].halfA = g[1].halfB = hf;
+  };
+  {
+    GemmArgs ga[4];
+    int n = 0;
+    if (!m->cfg.untied_ffn) {
+      ffn_grads(0, k * N, ga);
+      n = 2;
+    }
+    for (int r = 0; m->cfg.untied_ffn && r < k; ++r) {
+      ffn_grads(r, N, ga);
+      ok = launch_wgrads(ga, 2, red, wsx, capx, w) && ok;
+      launch_reduce_jobs(m->bf, red, 2, w);
+      wsx = m->gws2;
+      capx = m->gws2_cap;
+    }
+    ga[n] = gemm(D, 256, N, at(m->kY, (int64_t)k * N * D), 1, D, rb, m->dz, 256, 1, rb, gr + L.off[P_WOUT], 256, 0.f);
+    ga[n++].halfA = hf;
+    ga[n++] = gemm(D, D, N, m->kO, 1, D, rb, m->dY0, D, 1, rb, gr + L.at(P_WO, top), D, 0.f);
+    ok = launch_wgrads(ga, n, red, wsx, capx, w) && ok;
+    nred = n;
   }
-  // side: dWo = O^T . dY_0
-  launch_gemm(gemm(D, D, N, m->kO, 1, D, rb, m->dY0, D, 1, rb, gr + L.at(P_WO, top), D, 0.f), ws2, m->gws_cap, w);
   // sP: [0, T D) sum over windows of dK, [T D, 2T D) of dV (from the attention
   // backward), [2T D, (2T+1) D) of dQ, [(2T+1) D, (2T+2) D) of dY_0
   float* sK = m->sP;
@@ -921,7 +950,7 @@ extern "C" int trace_adapt_step(trace_model* m, void* stream) {
       g.r1round = value ? rb : 0;
       g.r1scale = value ? 1.f : ascale;
     }
-    return launch_gemm(g, ws2, m->gws_cap, w);
+    return g;
   };
   if (m->cfg.use_pos && !sums1) launch_colsum(m->dQ, N, D, D, sQ, 0.f, m->cws, s);
   order(m, s, w);  // dQ, dK, dV and their sums over windows are complete
@@ -929,39 +958,63 @@ extern "C" int trace_adapt_step(trace_model* m, void* stream) {
   // G^T dZ as GEMMs on the byte-embedding part G, then P^T (sum over windows of
   // dZ) for the positional part
   if (NL == 1) {
-    // rank1: both from the per-window sums over the tokens (one launch; xlast:
-    // their rows gathered in it, Xk holding the last tokens only)
+    // red: dWk, dWv, dWq
+    RedJob* rk = red + nred;
+    const int64_t kvws = rank1 ? kv_wgrad_ws_floats(N, T, D, H) : 0;
+    // rank1: dWk, dWv from the per-window sums over the tokens (xlast: their rows
+    // gathered in that kernel, Xk holding the last tokens only)
+    bool kv = false;
     if (xlast) {
-      ok = launch_kv_wgrad(nullptr, m->kwin, (const uint16_t*)m->Ec, m->cfg.e, m->cfg.g, m->dSc, m->kA, m->kq, m->dO,
-                           N, T, D, H, ascale, ws2, m->gws_cap, gr + L.at(P_WK, top), gr + L.at(P_WV, top), w) &&
-           ok;
-    } else if (!(rank1 && launch_kv_wgrad((const uint16_t*)m->Xk, nullptr, nullptr, 8, 1, m->dSc, m->kA, m->kq,
-                                          m->dO, N, T, D, H, ascale, ws2, m->gws_cap, gr + L.at(P_WK, top),
-                                          gr + L.at(P_WV, top), w))) {
-      ok = kv_grad(m->Xk, 1, D, hf, false, gr + L.at(P_WK, top)) && ok;
-      ok = kv_grad(m->Xk, 1, D, hf, true, gr + L.at(P_WV, top)) && ok;
+      kv = launch_kv_wgrad(nullptr, m->kwin, (const uint16_t*)m->Ec, m->cfg.e, m->cfg.g, m->dSc, m->kA, m->kq, m->dO,
+                           N, T, D, H, ascale, wsx, capx, gr + L.at(P_WK, top), gr + L.at(P_WV, top), w, rk);
+      ok = kv && ok;
+    } else if (rank1) {
+      kv = launch_kv_wgrad((const uint16_t*)m->Xk, nullptr, nullptr, 8, 1, m->dSc, m->kA, m->kq, m->dO, N, T, D, H,
+                           ascale, wsx, capx, gr + L.at(P_WK, top), gr + L.at(P_WV, top), w, rk);
+    }
+    if (kv) {
+      wsx += kvws;
+      capx -= kvws;
     }
     // side: dWq = X_last^T dQ; Xk was written on this stream, dQ before the last mark
-    GemmArgs gq = xlast ? gemm(D, D, N, m->Xk, 1, D, rb, m->dQ, D, 1, 0, gr + L.at(P_WQ, top), D, 0.f)
-                        : gemm(D, D, N, at(m->Xk, (int64_t)(T - 1) * D), 1, (int64_t)T * D, rb, m->dQ, D, 1, 0,
-                               gr + L.at(P_WQ, top), D, 0.f);
-    gq.halfA = hf;
-    ok = launch_gemm(gq, ws2, m->gws_cap, w) && ok;
-    if (m->cfg.use_pos) {
-      // the positional parts of dWk, dWv, dWq in one launch
-      const float* S3[3] = {sK, sV, sQ};
-      const int t03[3] = {0, 0, T - 1}, nt3[3] = {T, T, 1};
-      float* dW3[3] = {gr + L.at(P_WK, top), gr + L.at(P_WV, top), gr + L.at(P_WQ, top)};
-      launch_pos_grad3(m->bf, m->Pc, S3, t03, nt3, dW3, 3, D, w);
+    GemmArgs g3[3];
+    g3[0] = kv_grad(m->Xk, 1, D, hf, false, gr + L.at(P_WK, top));
+    g3[1] = kv_grad(m->Xk, 1, D, hf, true, gr + L.at(P_WV, top));
+    g3[2] = xlast ? gemm(D, D, N, m->Xk, 1, D, rb, m->dQ, D, 1, 0, gr + L.at(P_WQ, top), D, 0.f)
+                  : gemm(D, D, N, at(m->Xk, (int64_t)(T - 1) * D), 1, (int64_t)T * D, rb, m->dQ, D, 1, 0,
+                         gr + L.at(P_WQ, top), D, 0.f);
+    g3[2].halfA = hf;
+    if (m->bf) {
+      for (int i = kv ? 2 : 0; i < 3; ++i) {
+        // (the last one's sums may wait in the workspace)
+        if (i == 2)
+          g3[i].defer = rk + i;
+        else
+          rk[i] = whole_product(g3[i]);
+        ok = launch_gemm(g3[i], wsx, capx, w) && ok;
+      }
+    } else {
+      ok = launch_wgrads(g3, 3, rk, wsx, capx, w) && ok;
     }
+    if (m->cfg.use_pos) {  // the positional parts, added with the sums
+      const float* S3[3] = {sK, sV, sQ};
+      for (int i = 0; i < 3; ++i) {
+        rk[i].P = m->Pc;
+        rk[i].S = S3[i];
+        rk[i].t0 = i == 2 ? T - 1 : 0;
+        rk[i].nt = i == 2 ? 1 : T;
+      }
+    }
+    nred += 3;
   } else {
     // the top layer's input: the layer below's output, rounded (bf16 storage point)
-    ok = kv_grad(Xtop, 1, D, false, false, gr + L.at(P_WK, top)) && ok;
-    ok = kv_grad(Xtop, 1, D, false, true, gr + L.at(P_WV, top)) && ok;
+    ok = launch_gemm(kv_grad(Xtop, 1, D, false, false, gr + L.at(P_WK, top)), wsx, capx, w) && ok;
+    ok = launch_gemm(kv_grad(Xtop, 1, D, false, true, gr + L.at(P_WV, top)), wsx, capx, w) && ok;
     ok = launch_gemm(gemm(D, D, N, Xtop + (int64_t)(T - 1) * D, 1, (int64_t)T * D, rb, m->dQ, D, 1, 0,
                           gr + L.at(P_WQ, top), D, 0.f),
-                     ws2, m->gws_cap, w) && ok;
+                     wsx, capx, w) && ok;
   }
+  launch_reduce_jobs(m->bf, red, nred, w);
   // dX = dK Wk^T + dV Wv^T (+ dQ Wq^T + dY_0 on the last token).  bf16 models
   // form the key and value part from the rank-one rows of dK and dV
   // (launch_dx_rank1, which adds dY_0); otherwise two products over every token

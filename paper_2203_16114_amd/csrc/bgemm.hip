@@ -273,22 +273,25 @@ __device__ __forceinline__ void store_tile(const float4 (&vin)[8], uint32_t mask
   }
 }
 
-// C[m][n] (+)= sum_k A(m, k) B(k, n) over this split's k range.  AKC / BKC:
-// that operand's contiguous dimension is k; SA / SB: that operand is split.
-// 1-D grid of tn * tm * splits blocks.
+// Workgroups go to the 8 XCDs in turn: give each XCD a run of consecutive
+// tiles (n fastest), which share rows of A and k ranges of B.
+__device__ __forceinline__ int tile_of_block() {
+  const int nb = (int)gridDim.x, b = (int)blockIdx.x, per = nb / 8;
+  return b < per * 8 ? (b & 7) * per + (b >> 3) : b;
+}
+
+// C[m][n] (+)= sum_k A(m, k) B(k, n) over the k range of tile L of tn * tm * splits.
+// AKC / BKC: that operand's contiguous dimension is k; SA / SB: that operand is
+// split.  lds: two stages of tiles A hi, B hi, [A lo | B lo].
 template <bool AKC, bool BKC, bool SA, bool SB, bool HA, bool HB>
-__global__ __launch_bounds__(256) void k_bgemm(Src A, Src B, int Kp, int M, int N, float* C, int64_t ldc,
-                                               float beta, float* __restrict__ part, int kchunk, int tn, int tm,
-                                               const float* __restrict__ gu, int hc, const float* cin) {
+__device__ __forceinline__ void bgemm_tile(uint4 (&lds)[2][2 + SA + SB][UNITS], int L, const Src& A, const Src& B, int Kp,
+                                           int M, int N, float* C, int64_t ldc, float beta, float* __restrict__ part,
+                                           int kchunk, int tn, int tm, const float* __restrict__ gu, int hc,
+                                           const float* cin) {
   static_assert(!(SA && SB), "at most one operand is split");
-  constexpr int NT = 2 + (SA ? 1 : 0) + (SB ? 1 : 0);  // tiles per stage: A hi, B hi, [A lo | B lo]
-  __shared__ uint4 lds[2][NT][UNITS];
+  constexpr int NT = 2 + (SA ? 1 : 0) + (SB ? 1 : 0);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lg = lane >> 4, lc = lane & 15;
   const int wm = wave >> 1, wn = wave & 1;
-  // workgroups go to the 8 XCDs in turn: give each XCD a run of consecutive
-  // tiles (n fastest), which share rows of A and k ranges of B
-  const int nb = (int)gridDim.x, b = (int)blockIdx.x, per = nb / 8;
-  const int L = b < per * 8 ? (b & 7) * per + (b >> 3) : b;
   const int bx = L % tn, by = (L / tn) % tm, bz = L / (tn * tm);
   const int m0 = by * BM, n0 = bx * BN;
   const int kb = bz * kchunk, ke = min(Kp, kb + kchunk);
@@ -425,6 +428,47 @@ __global__ __launch_bounds__(256) void k_bgemm(Src A, Src B, int Kp, int M, int 
         }
       }
   }
+}
+
+// 1-D grid of tn * tm * splits blocks.
+template <bool AKC, bool BKC, bool SA, bool SB, bool HA, bool HB>
+__global__ __launch_bounds__(256) void k_bgemm(Src A, Src B, int Kp, int M, int N, float* C, int64_t ldc,
+                                               float beta, float* __restrict__ part, int kchunk, int tn, int tm,
+                                               const float* __restrict__ gu, int hc, const float* cin) {
+  __shared__ uint4 lds[2][2 + SA + SB][UNITS];
+  bgemm_tile<AKC, BKC, SA, SB, HA, HB>(lds, tile_of_block(), A, B, Kp, M, N, C, ldc, beta, part, kchunk, tn, tm, gu, hc,
+                                       cin);
+}
+
+// Several weight gradients (rows of both operands contiguous, neither split) in
+// one launch: at a few thousand windows each fills half the chip for 10-15 us and
+// the host takes 4 us to launch it.  mode: bit 0 A stored as bf16, bit 1 B.
+struct BJob {
+  Src A, B;
+  int Kp, M, N, kchunk, tn, tm, mode, tile0;  // tile0: first tile of the job in the grid
+  float *C, *part;
+  int64_t ldc;
+};
+struct BGroup {
+  BJob j[GROUP_MAX_JOBS];
+  int n;
+};
+__global__ __launch_bounds__(256) void k_bgemm_group(BGroup g) {
+  __shared__ uint4 lds[2][2][UNITS];
+  const int L = tile_of_block();
+  int q = 0;
+  for (int u = 1; u < g.n; ++u) q = L >= g.j[u].tile0 ? u : q;
+  const BJob& j = g.j[q];
+  const int t = L - j.tile0;
+  if (j.mode == 3)
+    bgemm_tile<false, false, false, false, true, true>(lds, t, j.A, j.B, j.Kp, j.M, j.N, j.C, j.ldc, 0.f, j.part, j.kchunk,
+                                                       j.tn, j.tm, nullptr, 0, nullptr);
+  else if (j.mode == 1)
+    bgemm_tile<false, false, false, false, true, false>(lds, t, j.A, j.B, j.Kp, j.M, j.N, j.C, j.ldc, 0.f, j.part,
+                                                        j.kchunk, j.tn, j.tm, nullptr, 0, nullptr);
+  else
+    bgemm_tile<false, false, false, false, false, false>(lds, t, j.A, j.B, j.Kp, j.M, j.N, j.C, j.ldc, 0.f, j.part,
+                                                         j.kchunk, j.tn, j.tm, nullptr, 0, nullptr);
 }
 
 // ---- 256 x 256 tiles, 512 threads (8 waves, two per SIMD), 32 k per stage ----
@@ -915,6 +959,16 @@ int64_t bgemm_ws_floats(int M, int N, int K) {
   return s > 1 ? (int64_t)s * M * N : 0;
 }
 
+int64_t bgemm_group_ws_floats(int M, int N, int K) {
+  // the most of any batch up to K that the 256-tile kernel does not take
+  const int tiles = (int)(rup(M, big::TM) / big::TM * (rup(N, big::TN) / big::TN));
+  int q = 1;  // that kernel's split there
+  while (tiles * q < 256) q *= 2;
+  const int Kb = q * 1024;
+  const int s = bgemm_splits(M, N, (int)rup(std::min(K, Kb), BK));
+  return s > 1 ? (int64_t)s * M * N : 0;
+}
+
 bool launch_bgemm(const GemmArgs& g, const GemmArgs* g2, float* ws, int64_t ws_cap, hipStream_t s, int force) {
   if (!g.roundA && !g.roundB) return false;  // fp32 operands on both sides: not this kernel
   if (g2 && (g2->M != g.M || g2->N != g.N || g2->roundA != g.roundA || g2->roundB != g.roundB ||
@@ -990,6 +1044,71 @@ bool launch_bgemm(const GemmArgs& g, const GemmArgs* g2, float* ws, int64_t ws_c
     else
       launch_orient<false, false>(sa, sb, ha, hb, grid, A, B, Kp, g, part, kchunk, tn, tm, s);
   }
-  if (splits > 1) launch_splitk_reduce(ws, splits, g.M, g.N, g.C, g.ldc, g.beta, g.Cin, s);
+  if (splits > 1 && g.defer && g.beta == 0.f) {
+    g.defer->part = ws;
+    g.defer->pstride = (int64_t)g.M * g.N;
+    g.defer->splits = splits;
+  } else if (splits > 1) {
+    launch_splitk_reduce(ws, splits, g.M, g.N, g.C, g.ldc, g.beta, g.Cin, s);
+  }
   return true;
+}
+
+void launch_bgemm_group(const GemmArgs* g, int n, bool* grouped, RedJob* red, float*& ws, int64_t& ws_cap, bool plan,
+                        hipStream_t s) {
+  BGroup G{};
+  int tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    const GemmArgs& a = g[i];
+    grouped[i] = false;
+    // both operands at a storage point; the 256-tile kernel keeps what fills the chip there
+    if (!a.roundA || !a.roundB || (a.halfB && !a.halfA) || a.r1c || a.gelu_u || a.halfC || a.beta != 0.f || a.K <= 0)
+      continue;
+    if (big::splits(a.M, a.N, (int)rup(a.K, big::TK)) > 0) continue;
+    Src A{}, B{};
+    bool akc = false, bkc = false;
+    if (!add_segment(A, 0, a.A, a.sam, a.sak, a.M, a.K, akc, a.halfA) ||
+        !add_segment(B, 0, a.B, a.sbn, a.sbk, a.N, a.K, bkc, a.halfB) || akc || bkc)
+      continue;
+    grouped[i] = true;
+    if (plan) continue;
+    A.p1 = A.p0;
+    A.ld1 = A.ld0;
+    B.p1 = B.p0;
+    B.ld1 = B.ld0;
+    const int Kp = (int)rup(a.K, BK);
+    A.k1p = B.k1p = Kp;
+    int splits = bgemm_splits(a.M, a.N, Kp);
+    while (splits > 1 && (int64_t)splits * a.M * a.N > ws_cap) splits /= 2;
+    const int kchunk = (int)rup((Kp + splits - 1) / splits, BK);
+    splits = (Kp + kchunk - 1) / kchunk;
+    BJob& j = G.j[G.n++];
+    j.A = A;
+    j.B = B;
+    j.Kp = Kp;
+    j.M = a.M;
+    j.N = a.N;
+    j.kchunk = kchunk;
+    j.tn = (int)(rup(a.N, BN) / BN);
+    j.tm = (int)(rup(a.M, BM) / BM);
+    j.mode = (a.halfA ? 1 : 0) | (a.halfB ? 2 : 0);
+    j.tile0 = tiles;
+    j.C = a.C;
+    j.ldc = a.ldc;
+    j.part = splits > 1 ? ws : nullptr;
+    tiles += j.tn * j.tm * splits;
+    red[i] = RedJob{};
+    red[i].part = splits > 1 ? ws : a.C;
+    red[i].pstride = (int64_t)a.M * a.N;
+    red[i].splits = splits;
+    red[i].M = a.M;
+    red[i].N = a.N;
+    red[i].C = a.C;
+    red[i].ldc = a.ldc;
+    if (splits > 1) {
+      ws += (int64_t)splits * a.M * a.N;
+      ws_cap -= (int64_t)splits * a.M * a.N;
+    }
+  }
+  if (G.n) hipLaunchKernelGGL(k_bgemm_group, dim3((unsigned)tiles), dim3(256), 0, s, G);
 }

@@ -369,8 +369,113 @@ void launch_splitk_reduce(const float* ws, int splits, int M, int N, float* C, i
                        beta, cin);
 }
 
+// Several split-K sums and positional parts in one launch (RedJob), four
+// consecutive n per thread, eight partials in flight; each sum in the order of
+// k_splitk_reduce4, the positional terms added to it in u order (summed first).
+struct RedArgs {
+  RedJob j[RED_MAX_JOBS];
+  int b0[RED_MAX_JOBS + 1];  // first block of each job
+  int n;
+};
+template <bool BF>
+__global__ __launch_bounds__(256) void k_reduce_jobs(RedArgs a) {
+  typedef Mma<BF> M;
+  int q = 0;
+  for (int u = 1; u < a.n; ++u) q = (int)blockIdx.x >= a.b0[u] ? u : q;
+  const RedJob& j = a.j[q];
+  const uint32_t i = (blockIdx.x - a.b0[q]) * 256u + threadIdx.x, n4 = (uint32_t)j.N >> 2;
+  if (i >= (uint32_t)j.M * n4) return;
+  const uint32_t m = i / n4, n = (i - m * n4) * 4;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto add = [&](const float4& v) {
+    s.x += v.x;
+    s.y += v.y;
+    s.z += v.z;
+    s.w += v.w;
+  };
+  // (a product that is already whole is read back from C)
+  const float* p = j.part + (j.splits > 1 ? (int64_t)m * j.N : (int64_t)m * j.ldc) + n;
+  int z = 0;
+  for (; z + 8 <= j.splits; z += 8) {
+    float4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(p + (int64_t)(z + u) * j.pstride);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) add(v[u]);
+  }
+  for (; z < j.splits; ++z) add(*reinterpret_cast<const float4*>(p + (int64_t)z * j.pstride));
+  if (j.nt) {
+    const typename M::T* P = (const typename M::T*)j.P;
+    float4 c = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int u = 0; u < j.nt; ++u) {
+      const float w = M::val(P[(int64_t)(j.t0 + u) * j.M + m]);
+      const float4 x = *reinterpret_cast<const float4*>(j.S + (int64_t)u * j.N + n);
+      c.x += w * x.x;
+      c.y += w * x.y;
+      c.z += w * x.z;
+      c.w += w * x.w;
+    }
+    add(c);
+  }
+  *reinterpret_cast<float4*>(j.C + (int64_t)m * j.ldc + n) = s;
+}
+// (N and ldc are multiples of 4 and every pointer 16-byte aligned: the weight
+// gradients of a model's flat layout)
+void launch_reduce_jobs(bool bf, const RedJob* jobs, int n, hipStream_t s) {
+  RedArgs a{};
+  int b = 0;
+  for (int i = 0; i < n; ++i) {
+    if (jobs[i].splits <= 1 && jobs[i].nt == 0) continue;  // C is whole
+    a.j[a.n] = jobs[i];
+    a.b0[a.n++] = b;
+    b += (int)(((int64_t)jobs[i].M * (jobs[i].N / 4) + 255) / 256);
+  }
+  if (!a.n) return;
+  if (bf)
+    hipLaunchKernelGGL(k_reduce_jobs<true>, dim3((unsigned)b), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_reduce_jobs<false>, dim3((unsigned)b), dim3(256), 0, s, a);
+}
+
+int64_t wgrad_ws_floats(bool bf, int M, int N, int K) {
+  return bf ? bgemm_group_ws_floats(M, N, K) : fgemm_ws_floats(M, N, K);
+}
+
+RedJob whole_product(const GemmArgs& g) {
+  RedJob r{};
+  r.part = r.C = g.C;
+  r.splits = 1;
+  r.M = g.M;
+  r.N = g.N;
+  r.ldc = g.ldc;
+  return r;
+}
+
+bool launch_wgrads(const GemmArgs* g, int n, RedJob* red, float*& ws, int64_t& ws_cap, hipStream_t s) {
+  if (n < 1 || n > GROUP_MAX_JOBS) return false;
+  const bool bf = g[0].roundA || g[0].roundB;
+  bool grouped[GROUP_MAX_JOBS], ok = true;
+  auto group = [&](bool plan) {
+    if (bf)
+      launch_bgemm_group(g, n, grouped, red, ws, ws_cap, plan, s);
+    else
+      launch_fgemm_group(g, n, grouped, red, ws, ws_cap, plan, s);
+  };
+  group(true);
+  // the others first, each with its own split-K pass: the grouped products' sums
+  // then wait in the same workspace (one stream)
+  for (int i = 0; i < n; ++i) {
+    if (grouped[i]) continue;
+    ok = launch_gemm(g[i], ws, ws_cap, s) && ok;
+    red[i] = whole_product(g[i]);
+  }
+  group(false);
+  return ok;
+}
+
 bool launch_gemm(const GemmArgs& g0, float* ws, int64_t ws_cap, hipStream_t s) {
   if (g0.M <= 0 || g0.N <= 0) return true;
+  if (g0.defer) *g0.defer = whole_product(g0);
   // bf16 storage points on at least one side: register-staged bf16 GEMM
   if (launch_bgemm(g0, nullptr, ws, ws_cap, s)) return true;
   // fp32 operands on both sides: the k-split kernel of small products
@@ -1426,7 +1531,7 @@ bool kv_wgrad_ready(int64_t N, int T, int D, int H, int e, int64_t ws_cap) {
 
 bool launch_kv_wgrad(const uint16_t* X, const uint8_t* win, const uint16_t* E, int e, int g, const float* dS,
                      const float* A, const float* q, const float* dO, int64_t N, int T, int D, int H, float scale,
-                     float* ws, int64_t ws_cap, float* dWk, float* dWv, hipStream_t s) {
+                     float* ws, int64_t ws_cap, float* dWk, float* dWv, hipStream_t s, RedJob* red) {
   if (!kv_wgrad_ready(N, T, D, H, win ? e : 8, ws_cap) || (!win && !X)) return false;
   if (dWv != dWk + (int64_t)D * D) return false;  // one split-K pass for both
   if (((uintptr_t)X | (uintptr_t)E | (uintptr_t)dS | (uintptr_t)A | (uintptr_t)q | (uintptr_t)dO | (uintptr_t)ws) & 15)
@@ -1452,7 +1557,19 @@ bool launch_kv_wgrad(const uint16_t* X, const uint8_t* win, const uint16_t* E, i
   TRACE_KVW(4, 64, 8) TRACE_KVW(8, 64, 8)
 #undef TRACE_KVW
   // the two gradients as one [2 D][D] product
-  launch_splitk_reduce(ws, S, 2 * D, D, dWk, D, 0.f, nullptr, s);
+  if (red) {
+    for (int i = 0; i < 2; ++i) {
+      red[i] = RedJob{};
+      red[i].part = ws + (int64_t)i * D * D;
+      red[i].pstride = (int64_t)2 * D * D;
+      red[i].splits = S;
+      red[i].M = red[i].N = D;
+      red[i].C = i ? dWv : dWk;
+      red[i].ldc = D;
+    }
+  } else {
+    launch_splitk_reduce(ws, S, 2 * D, D, dWk, D, 0.f, nullptr, s);
+  }
   return true;
 }
 
@@ -2091,46 +2208,6 @@ void launch_pos_grad(bool bf, const void* P, const float* S, int t0, int nt, int
     hipLaunchKernelGGL(k_pos_grad<true>, grid, dim3(256), 0, s, (const uint16_t*)P, S, t0, nt, D, dW);
   else
     hipLaunchKernelGGL(k_pos_grad<false>, grid, dim3(256), 0, s, (const float*)P, S, t0, nt, D, dW);
-}
-
-// Up to three positional parts in one launch (blockIdx.y = the job), each as
-// k_pos_grad computes it.
-struct PosGradJobs {
-  const float* S[3];
-  float* dW[3];
-  int t0[3], nt[3];
-};
-template <bool BF>
-__global__ void k_pos_grad3(const typename Mma<BF>::T* __restrict__ P, PosGradJobs jb, int D) {
-  typedef Mma<BF> M;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (int64_t)D * D) return;
-  const int y = blockIdx.y;
-  // the job's fields, selected with constant indexes (blockIdx.y is uniform)
-  const float* S = y == 0 ? jb.S[0] : (y == 1 ? jb.S[1] : jb.S[2]);
-  float* dW = y == 0 ? jb.dW[0] : (y == 1 ? jb.dW[1] : jb.dW[2]);
-  const int t0 = y == 0 ? jb.t0[0] : (y == 1 ? jb.t0[1] : jb.t0[2]);
-  const int nt = y == 0 ? jb.nt[0] : (y == 1 ? jb.nt[1] : jb.nt[2]);
-  const int r = (int)(i / D), c = (int)(i % D);
-  float acc = 0.f;
-  for (int u = 0; u < nt; ++u) acc += M::val(P[(t0 + u) * D + r]) * S[u * D + c];
-  dW[i] += acc;
-}
-void launch_pos_grad3(bool bf, const void* P, const float* const* S, const int* t0, const int* nt, float* const* dW,
-                      int njobs, int D, hipStream_t s) {
-  if (njobs < 1 || njobs > 3) return;
-  PosGradJobs jb{};
-  for (int j = 0; j < njobs; ++j) {
-    jb.S[j] = S[j];
-    jb.dW[j] = dW[j];
-    jb.t0[j] = t0[j];
-    jb.nt[j] = nt[j];
-  }
-  const dim3 grid((unsigned)(((int64_t)D * D + 255) / 256), (unsigned)njobs);
-  if (bf)
-    hipLaunchKernelGGL(k_pos_grad3<true>, grid, dim3(256), 0, s, (const uint16_t*)P, jb, D);
-  else
-    hipLaunchKernelGGL(k_pos_grad3<false>, grid, dim3(256), 0, s, (const float*)P, jb, D);
 }
 
 // -------------------------------------------------------------------- Adam ----

@@ -68,13 +68,12 @@ __device__ __forceinline__ uint4 bits4(const float4& v) {
 
 // Tiles of 16 F x 16 F; U k-steps (of 16) per batch of loads.
 template <bool AKC, bool BKC, int F, int U>
-__global__ __launch_bounds__(512) void k_fgemm(FArgs a) {
+__device__ __forceinline__ void fgemm_tile(float (&red)[8][16 * F * (16 * F + 4)], int tile, int zi, const FArgs& a) {
   typedef Mma<false> M;
   constexpr int TS = 16 * F, STR = TS + 4;
-  __shared__ __align__(16) float red[8][TS * STR];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lg = lane >> 4, lc = lane & 15;
-  const int m0 = ((int)blockIdx.x / a.tn) * TS, n0 = ((int)blockIdx.x % a.tn) * TS;
-  const int zb = (int)blockIdx.z * a.kz, ze = min(a.K, zb + a.kz);
+  const int m0 = (tile / a.tn) * TS, n0 = (tile % a.tn) * TS;
+  const int zb = zi * a.kz, ze = min(a.K, zb + a.kz);
   const int per = ((ze - zb + 127) / 128) * 16;  // k values per wave
   const int kb = zb + wave * per, ke = min(ze, kb + per);
   int ra[F], rb[F];
@@ -139,7 +138,7 @@ __global__ __launch_bounds__(512) void k_fgemm(FArgs a) {
     for (int w = 1; w < 8; ++w) v += red[w][i * STR + j];
     if (m < a.M && n < a.N) {
       if (a.part) {
-        a.part[((int64_t)blockIdx.z * a.M + m) * a.N + n] = v;
+        a.part[((int64_t)zi * a.M + m) * a.N + n] = v;
         continue;
       }
       const int64_t o = (int64_t)m * a.ldc + n;
@@ -148,6 +147,28 @@ __global__ __launch_bounds__(512) void k_fgemm(FArgs a) {
       a.C[o] = v;
     }
   }
+}
+
+template <bool AKC, bool BKC, int F, int U>
+__global__ __launch_bounds__(512) void k_fgemm(FArgs a) {
+  __shared__ __align__(16) float red[8][16 * F * (16 * F + 4)];
+  fgemm_tile<AKC, BKC, F, U>(red, (int)blockIdx.x, (int)blockIdx.z, a);
+}
+
+// Several weight gradients (rows of both operands contiguous) in one launch, on
+// 16-wide tiles: the host takes about 4 us to launch each
+struct FGroup {
+  FArgs j[GROUP_MAX_JOBS];
+  int tile0[GROUP_MAX_JOBS], tiles[GROUP_MAX_JOBS];  // first block, blocks per z of each job
+  int n;
+};
+__global__ __launch_bounds__(512) void k_fgemm_group(FGroup g) {
+  __shared__ __align__(16) float red[8][16 * 20];
+  const int b = (int)blockIdx.x;
+  int q = 0;
+  for (int u = 1; u < g.n; ++u) q = b >= g.tile0[u] ? u : q;
+  const int t = b - g.tile0[q];
+  fgemm_tile<false, false, 1, 4>(red, t % g.tiles[q], t / g.tiles[q], g.j[q]);
 }
 
 bool seg(FSrc& s, int i, const float* p, int64_t srow, int64_t sk, int rows, int K, bool& kc) {
@@ -184,6 +205,18 @@ void launch(bool akc, bool bkc, const FArgs& a, dim3 grid, hipStream_t s) {
 // 512 x 128 x 8192 (2^29) 61 / 47; 4096 x 1024 x 256 (2^30) 65-108 / 40-51.
 constexpr int64_t FGEMM_MAX = (int64_t)1 << 28;
 
+// Blocks along k of a product of `tiles` tiles: cut while that makes at most 512
+// blocks of at least 1024 k values each.
+static int z_blocks(int64_t tiles, int M, int N, int K, int64_t ws_cap) {
+  int z = 1;
+  while (tiles * z < 512 && K / (2 * z) >= 1024 && (int64_t)2 * z * M * N <= ws_cap) z *= 2;
+  return z;
+}
+int64_t fgemm_ws_floats(int M, int N, int K) {
+  const int z = z_blocks((int64_t)((M + 15) / 16) * ((N + 15) / 16), M, N, K, (int64_t)1 << 60);
+  return z > 1 ? (int64_t)z * M * N : 0;
+}
+
 bool launch_fgemm(const GemmArgs& g, const GemmArgs* g2, float* ws, int64_t ws_cap, hipStream_t s) {
   if (g.roundA || g.roundB || g.halfA || g.halfB || g.halfC || g.r1c || g.rowwise || g.K <= 0) return false;
   if (g2 && (g2->roundA || g2->roundB || g2->halfA || g2->halfB || g2->r1c || g2->K <= 0 || g.K % 16)) return false;
@@ -215,9 +248,7 @@ bool launch_fgemm(const GemmArgs& g, const GemmArgs* g2, float* ws, int64_t ws_c
   const int ts = wide ? 32 : 16;
   a.tn = (g.N + ts - 1) / ts;
   const int64_t tiles = (int64_t)((g.M + ts - 1) / ts) * a.tn;
-  int z = 1;
-  if (!g.gelu_u)
-    while (tiles * z < 512 && K / (2 * z) >= 1024 && (int64_t)2 * z * g.M * g.N <= ws_cap) z *= 2;
+  int z = g.gelu_u ? 1 : z_blocks(tiles, g.M, g.N, K, ws_cap);
   a.kz = ((K + z - 1) / z + 15) / 16 * 16;
   z = (K + a.kz - 1) / a.kz;
   a.part = z > 1 ? ws : nullptr;
@@ -228,4 +259,54 @@ bool launch_fgemm(const GemmArgs& g, const GemmArgs* g2, float* ws, int64_t ws_c
     launch<1, 4>(akc, bkc, a, grid, s);
   if (z > 1) launch_splitk_reduce(ws, z, g.M, g.N, g.C, g.ldc, g.beta, g.Cin, s);
   return true;
+}
+
+void launch_fgemm_group(const GemmArgs* g, int n, bool* grouped, RedJob* red, float*& ws, int64_t& ws_cap, bool plan,
+                        hipStream_t s) {
+  FGroup G{};
+  int blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    const GemmArgs& a = g[i];
+    grouped[i] = false;
+    if (a.roundA || a.roundB || a.halfA || a.halfB || a.halfC || a.r1c || a.gelu_u || a.beta != 0.f || a.K <= 0) continue;
+    if ((int64_t)a.M * a.N * a.K > FGEMM_MAX) continue;
+    FArgs f{};
+    bool akc = false, bkc = false;
+    if (!seg(f.A, 0, a.A, a.sam, a.sak, a.M, a.K, akc) || !seg(f.B, 0, a.B, a.sbn, a.sbk, a.N, a.K, bkc) || akc || bkc)
+      continue;
+    grouped[i] = true;
+    if (plan) continue;
+    f.A.p1 = f.A.p0;
+    f.A.ld1 = f.A.ld0;
+    f.B.p1 = f.B.p0;
+    f.B.ld1 = f.B.ld0;
+    f.K = f.k1 = a.K;
+    f.M = a.M;
+    f.N = a.N;
+    f.C = a.C;
+    f.ldc = a.ldc;
+    f.tn = (a.N + 15) / 16;
+    const int tiles = (a.M + 15) / 16 * f.tn;
+    int z = z_blocks(tiles, a.M, a.N, a.K, ws_cap);
+    f.kz = ((a.K + z - 1) / z + 15) / 16 * 16;
+    z = (a.K + f.kz - 1) / f.kz;
+    f.part = z > 1 ? ws : nullptr;
+    G.j[G.n] = f;
+    G.tile0[G.n] = blocks;
+    G.tiles[G.n++] = tiles;
+    blocks += tiles * z;
+    red[i] = RedJob{};
+    red[i].part = z > 1 ? ws : a.C;
+    red[i].pstride = (int64_t)a.M * a.N;
+    red[i].splits = z;
+    red[i].M = a.M;
+    red[i].N = a.N;
+    red[i].C = a.C;
+    red[i].ldc = a.ldc;
+    if (z > 1) {
+      ws += (int64_t)z * a.M * a.N;
+      ws_cap -= (int64_t)z * a.M * a.N;
+    }
+  }
+  if (G.n) hipLaunchKernelGGL(k_fgemm_group, dim3((unsigned)blocks), dim3(512), 0, s, G);
 }

@@ -86,6 +86,26 @@ constexpr int REFRESH_MAX_JOBS = 17;
 bool launch_refresh(bool bf, const RefreshJob* jobs, int n, hipStream_t s);
 
 // ---- backward building blocks (bwd.hip) ----
+// Split-K partial results waiting for their sum: C[m][n] = sum_z part[z * pstride
+// + m N + n] in z order (z < splits), then, with nt > 0, the positional part
+// + sum_{u < nt} P[t0 + u][m] S[u][n] (P: operand copy [T][M]; weight gradients of
+// the projections)
+struct RedJob {
+  const float* part;
+  int64_t pstride;
+  int splits, M, N;
+  float* C;
+  int64_t ldc;
+  const void* P;
+  const float* S;
+  int t0, nt;
+};
+constexpr int RED_MAX_JOBS = 8;
+struct GemmArgs;
+RedJob whole_product(const GemmArgs& g);  // g.C is written already
+// all jobs in one launch; bf: P holds bf16 operand values
+void launch_reduce_jobs(bool bf, const RedJob* jobs, int n, hipStream_t s);
+
 struct GemmArgs {
   int M, N, K;
   const float* A;
@@ -117,7 +137,18 @@ struct GemmArgs {
   // forward products: a row's sum over k must not depend on the batch (M), so the
   // kernel that splits k for small batches (fgemm.hip) is not used
   int rowwise;
+  // nullable: where the product's partial sums wait is written there instead of
+  // their split-K pass (ws is then in use until launch_reduce_jobs)
+  RedJob* defer;
 };
+constexpr int GROUP_MAX_JOBS = 8;
+// Weight gradients C = A.B (A(m, k) contiguous along m, B(k, n) along n, beta 0,
+// no epilogue), as many as possible in one launch; red[i] describes where product
+// i's partial sums wait (splits 1 and part = C when C is written already); ws is
+// advanced past them (wgrad_ws_floats each let them reach their preferred split).
+// false as launch_gemm.
+bool launch_wgrads(const GemmArgs* g, int n, RedJob* red, float*& ws, int64_t& ws_cap, hipStream_t s);
+int64_t wgrad_ws_floats(bool bf, int M, int N, int K);
 // Deterministic: split-K partials are summed in a fixed order.  The split count
 // depends only on (M, N, K, ws_cap); gemm_ws_floats(M, N, K) floats let it
 // reach its preferred value.
@@ -137,6 +168,14 @@ int64_t bgemm_ws_floats(int M, int N, int K);
 // fgemm.hip: small products of fp32 operands; false (nothing launched) when the
 // product is not one it takes
 bool launch_fgemm(const GemmArgs& g, const GemmArgs* g2, float* ws, int64_t ws_cap, hipStream_t s);
+// those of the n weight gradients that one grouped launch of that kernel takes
+// (grouped[i] set; plan: nothing else), red[i] filled, ws advanced by their sums
+void launch_fgemm_group(const GemmArgs* g, int n, bool* grouped, RedJob* red, float*& ws, int64_t& ws_cap, bool plan,
+                        hipStream_t s);
+void launch_bgemm_group(const GemmArgs* g, int n, bool* grouped, RedJob* red, float*& ws, int64_t& ws_cap, bool plan,
+                        hipStream_t s);
+int64_t bgemm_group_ws_floats(int M, int N, int K);
+int64_t fgemm_ws_floats(int M, int N, int K);
 
 // bchain.hip: the input gradients from the kept logits down to dO in one launch
 struct ChainArgs {
@@ -189,7 +228,8 @@ int64_t kv_wgrad_ws_floats(int64_t N, int T, int D, int H);
 bool kv_wgrad_ready(int64_t N, int T, int D, int H, int e, int64_t ws_cap);
 bool launch_kv_wgrad(const uint16_t* X, const uint8_t* win, const uint16_t* E, int e, int g, const float* dS,
                      const float* A, const float* q, const float* dO, int64_t N, int T, int D, int H, float scale,
-                     float* ws, int64_t ws_cap, float* dWk, float* dWv, hipStream_t s);
+                     float* ws, int64_t ws_cap, float* dWk, float* dWv, hipStream_t s, RedJob* red = nullptr);
+// (red, two jobs: the split-K sums are left to launch_reduce_jobs)
 // sums over windows of the rank-one key and value gradients of the last query
 // row, of dQ and of dY0 into colsums [2 T + 2][D] (sK [T][D], sV [T][D], sQ, sY);
 // part: rank1_sums_part_floats floats (at most attn_bwd_part_floats); false when
@@ -214,9 +254,6 @@ bool launch_gather_last(const uint8_t* win, int64_t N, const uint16_t* E, int T,
                         hipStream_t s);
 // dW[i][j] += sum_{u < nt} P[t0 + u][i] * S[u][j]  (P: operand copy [T][D])
 void launch_pos_grad(bool bf, const void* P, const float* S, int t0, int nt, int D, float* dW, hipStream_t s);
-// up to three positional parts (launch_pos_grad's (S, t0, nt, dW)) in one launch
-void launch_pos_grad3(bool bf, const void* P, const float* const* S, const int* t0, const int* nt, float* const* dW,
-                      int njobs, int D, hipStream_t s);
 void launch_adam(float* theta, const float* grad, float* m, float* v, int64_t n, float lr, float b1, float b2,
                  float eps, float bc1, float bc2, hipStream_t s, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 
