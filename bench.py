@@ -187,16 +187,19 @@ def measure_forward(wid, steps_per_call, calls):
 
 
 def attn_kernel(w, steps_per_call):
-    """The attention kernel of a bf16 forward launch: one that shares the byte
-    groups between the windows of 64-position tiles, by head (k_attn_wh) at
-    d >= 128 where a stream's positions fill the tiles, or by alignment class
-    (k_attn_grp) for whole tiles at d = 64; else the per-token kernel (k_attn)."""
-    if w.dtype != "bf16" or w.g not in (4, 8):
+    """The attention kernel of a forward launch of workload w (all of its
+    streams): one that shares the byte groups between the windows of 64-position
+    tiles, by head (k_attn_wh), where a stream's positions fill the tiles, or by
+    alignment class (k_attn_grp) for whole tiles of bf16 d = 64; else the
+    per-token kernel (k_attn)."""
+    tiles, rows = -(-steps_per_call // 64), (64 + w.W - w.g + 15) // 16 * 16
+    if w.g not in (4, 8) or steps_per_call * (w.T + 1) < tiles * (rows + 64):
         return "k_attn"
-    if w.d >= 128 and (w.d, w.d // w.H) != (128, 64):
-        tiles, rows = -(-steps_per_call // 64), (64 + w.W - w.g + 15) // 16 * 16
-        return "k_attn_wh" if steps_per_call * (w.T + 1) >= tiles * (rows + 64) else "k_attn"
-    return "k_attn" if steps_per_call % 64 else "k_attn_grp"
+    if w.d <= 128 and w.B * steps_per_call <= (24576 if w.d == 64 else 6144):
+        return "k_attn"
+    if w.dtype == "bf16" and w.d == 64:
+        return "k_attn" if steps_per_call % 64 else "k_attn_grp"
+    return "k_attn_wh"
 
 
 def traffic_for(kernel, windows_per_launch):

@@ -157,11 +157,11 @@ int trace_init_flat_host(const trace_config* cfg, uint64_t seed, double std, flo
  * also keeps the activations of these n_streams*n_steps <= max_keep windows
  * for trace_adapt_step; TRACE_TOKEN_ATTN as above.  For a given attention
  * kernel, results depend only on each window's bytes and the weights (not on
- * n_streams, n_steps, chunking or position in the batch).  bf16 launches over
- * runs of about 20 positions or more (of each stream; the line depends on T and
- * g), without TRACE_TOKEN_ATTN, share byte groups between windows in a kernel
- * whose sums are ordered differently: their results agree with the other
- * launches' within rounding, not bit for bit. */
+ * n_streams, n_steps, chunking or position in the batch).  Larger calls over
+ * runs of about 20 positions or more of each stream (the lines depend on T, g
+ * and d), without TRACE_TOKEN_ATTN, share byte groups between windows in a
+ * kernel whose sums are ordered differently: their results agree with the other
+ * calls' within rounding, not bit for bit. */
 int trace_forward_bits(trace_model* m, const uint8_t* d_streams, int64_t stride, int32_t n_streams,
                        int64_t pos0, int32_t n_steps, float* d_bits, float* d_logits,
                        double* d_step_ce, uint32_t flags, void* stream);

@@ -717,6 +717,7 @@ int trace_forward_into(trace_model* m, const uint8_t* d_streams, int64_t stride,
     a.Wv = m->Wv;
     a.Wo = m->Wo;
     a.h0 = h0;
+    a.total = total;
     a.token_only = (flags & TRACE_TOKEN_ATTN) != 0 || m->nfeat != 0 || L.NL > 1;
     if (L.NL > 1) {  // the lower layers over every token row; the top reads their output
       const int64_t R = w.N * L.T;

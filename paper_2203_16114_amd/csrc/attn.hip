@@ -790,19 +790,19 @@ static bool launch_grp(const AttnArgs& a, hipStream_t s) {
   return false;
 }
 
-// bf16 launches over runs of positions share the byte groups unless the caller
+// Launches over runs of positions share the byte groups unless the caller
 // asks for the per-token kernel, whose result for a window does not depend on the
 // launch: k_attn_wh for the shapes it is built for and runs that fill its tiles,
-// k_attn_grp (d = 64, and d = 128 with heads of 64) when the
+// k_attn_grp (bf16, d = 64) when the
 // 64-window tiles each lie in one stream.  Launches too small to give every CU a
 // workgroup at the widest token tile (one step of the update path) take one
 // 16-row fragment per wave.
 template <bool BF, int T, int D, int DH>
 static void run_attn(const AttnArgs& a, hipStream_t s) {
-  if constexpr (BF) {
-    if (!a.kK && !a.token_only) {
-      if (launch_attn_wh(T, D, DH, a, s)) return;
-      if constexpr (D == 64 || (D == 128 && DH == 64)) {
+  if (!a.kK && !a.token_only) {
+    if (launch_attn_wh(BF, T, D, DH, a, s)) return;
+    if constexpr (BF) {
+      if constexpr (D == 64) {
         if (a.w.n_steps % 64 == 0 && a.w.n0 % 64 == 0) {
           if (a.g == 8 && launch_grp<T, 8, D, DH>(a, s)) return;
           if (a.g == 4 && launch_grp<T, 4, D, DH>(a, s)) return;

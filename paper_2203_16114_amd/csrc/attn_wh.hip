@@ -1,4 +1,4 @@
-// k_attn_wh: the attention block of attn.hip for bf16 launches over runs of
+// k_attn_wh: the attention block of attn.hip for launches over runs of
 // consecutive positions of each stream, with the byte groups shared between the
 // windows that hold them and the work cut by head: a wave forms everything of
 // its heads with no barrier until the output projection.
@@ -24,7 +24,7 @@
 //     16 lg + lc: softmax in the lane; shuffles hand the weights to the lanes
 //     that hold each window;
 //   V^T = Wv^T . X_E^T and O = sum_t a_t (V_E[row] + (P.Wv)[t]) with the same row
-//     selection, kept packed in bf16 until every wave is done with the group
+//     selection, kept as operand values until every wave is done with the group
 //     rows, over which the O tile is then written;
 //   h0^T = Wo^T . O^T + X_last (the waves split the output features), rows staged
 //     over the O tile and written whole.
@@ -32,7 +32,8 @@
 //
 // Workgroups have 4 waves (two workgroups per CU, whose vector and matrix phases
 // then interleave; the waves of one workgroup run the same phase together) except
-// at d = 512, where the group rows of one tile fill most of the LDS: 8 waves.
+// at 1024-byte rows (d = 512, fp32 d = 256), where the group rows of one tile fill most
+// of the LDS: 8 waves, and in models of fewer heads: one wave per head.
 //
 // Bound by the MFMAs and the vector work of scores and weighted sums (about half
 // of the cycles each at d = 256).  Measured against the kernels these launches
@@ -40,7 +41,8 @@
 // workgroup per CU) 1.244 -> 1.166 ms; 1021 streams x 203 positions (per-token
 // kernel) 690 -> 314 us; d = 512, 2^17 windows (per-token kernel, as the
 // shared-group tile did not fit the LDS) 1.494 -> 0.508 ms; d = 128, 2^18 windows
-// (shared-group kernel by alignment class) 186 -> 111 us.
+// (shared-group kernel by alignment class) 186 -> 111 us; fp32, d = 128, 2^16 windows
+// (per-token kernel; bound by its fp32 MFMAs, T times as many) 342 -> 105 us.
 #include <type_traits>
 
 #include "kcommon.h"
@@ -48,21 +50,31 @@
 
 namespace {
 
-template <int T, int G, int D, int DH, int NW_>
+template <bool BF, int T, int G, int D, int DH, int NW_>
 struct WhShape {
+  typedef Mma<BF> M;
+  static constexpr int ES = BF ? 2 : 4, EPU = 16 / ES;  // bytes per operand element, elements per 16-byte unit
   static constexpr int MA = 64, W = T * G, H = D / DH;
   static constexpr int NW = NW_, HPW = H / NW, NP = DH / 32;  // heads per wave, 32-feature parts per head
   static constexpr int NRF = (MA + W - G + 15) / 16;                        // group-row fragments
   static constexpr int NWF = MA / 16;                                       // window fragments
-  static constexpr int KSTEPS = D / 32, NB = D / 16;
-  static constexpr int XSTR = D * 2, XM = (D / 8 >= 16 ? 16 : D / 8) - 1;
+  static constexpr int KSTEPS = D / M::KS, NB = D / 16;
+  static constexpr int XSTR = D * ES, NUR = D / EPU, XM = (NUR >= 16 ? 16 : NUR) - 1;  // units per row, swizzle mask
   static constexpr int HSTR = D + 4;  // h0 rows staged for the write (floats, padded)
   static constexpr int XG = NRF * 16 * XSTR > MA * HSTR * 4 ? NRF * 16 * XSTR : MA * HSTR * 4;
   static constexpr int WB = NRF * 16 + G;
   static constexpr int PWS = T * DH;  // floats of one head's rows of P.Wk or P.Wv
   static constexpr int LDS = XG + NW * PWS * 4 + WB;
-  static constexpr bool ok = H % NW == 0 && H >= NW && HPW <= 2 && D >= 128 && LDS <= 160 * 1024;
+  static constexpr bool ok = H % NW == 0 && H >= NW && HPW <= 2 && LDS <= 160 * 1024;
 };
+
+// four consecutive operand elements as floats
+__device__ __forceinline__ f32x4 four(const uint16_t* p) {
+  const uint2 b = *reinterpret_cast<const uint2*>(p);
+  return f32x4{__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xffff0000u), __uint_as_float(b.y << 16),
+               __uint_as_float(b.y & 0xffff0000u)};
+}
+__device__ __forceinline__ f32x4 four(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 
 // x from lane (lc + S) % 16 of the same row of 16 lanes (DPP row_ror: lane i
 // receives lane i - n)
@@ -116,10 +128,12 @@ __device__ __forceinline__ void for_rows(const f32x4 (&acc)[NRF][2], int lc, con
   }
 }
 
-template <int T, int G, int D, int DH, int NW>
+template <bool BF, int T, int G, int D, int DH, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void k_attn_wh(AttnArgs a, int64_t t0, int tps) {
-  typedef Mma<true> M;
-  typedef WhShape<T, G, D, DH, NW> S;
+  typedef Mma<BF> M;
+  typedef typename M::T OT;
+  typedef WhShape<BF, T, G, D, DH, NW> S;
+  constexpr int ES = S::ES, EPU = S::EPU, NUR = S::NUR;
   constexpr int HPW = S::HPW, NP = S::NP, MA = S::MA, W = S::W, NRF = S::NRF, NWF = S::NWF;
   constexpr int KSTEPS = S::KSTEPS, NB = S::NB, XSTR = S::XSTR, XM = S::XM, HSTR = S::HSTR, NT = 64 * NW;
   constexpr int EPB = D / G;         // features per byte embedding
@@ -137,8 +151,8 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_wh(AttnArgs a, int64_t t0, 
   const int64_t l0 = st * a.w.n_steps + s0 - a.w.n0;       // local index of window 0
   if (l0 >= a.w.N || l0 + nv <= 0) return;
   const int i_lo = (int)max((int64_t)0, -l0), i_hi = (int)min((int64_t)nv, a.w.N - l0);  // windows stored
-  const uint16_t* __restrict__ E = (const uint16_t*)a.E;
-  const uint16_t* __restrict__ P = (const uint16_t*)a.P;
+  const OT* __restrict__ E = (const OT*)a.E;
+  const OT* __restrict__ P = (const OT*)a.P;
 
   // the tile's bytes: Wb[k] = stream byte at (target of window 0) - W + k, zero
   // past the last window's
@@ -147,22 +161,23 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_wh(AttnArgs a, int64_t t0, 
     for (int k = tid; k < S::WB; k += NT) Wb[k] = k < nv + W - 1 ? src[k] : 0;
   }
   __syncthreads();
-  // group rows o: unit u holds features 8u .. 8u + 7, from byte o + u / (EPB / 8)
+  // group rows o: unit u holds features EPU u .. + EPU - 1, from byte o + u / (units per byte)
   {
-    constexpr int NUT = NRF * 16 * (D / 8) / NT, NU = NUT > 16 ? NUT / 2 : NUT;  // in batches of at most 16 loads
-    static_assert(NRF * 16 * (D / 8) % NT == 0 && NUT % NU == 0, "group rows");
-#pragma unroll
+    constexpr int UPB = EPB / EPU;
+    constexpr int NUT = NRF * 16 * NUR / NT, NU = NUT > 16 ? NUT / 2 : NUT;  // all or half of the loads in flight
+    static_assert(NRF * 16 * NUR % NT == 0 && NUT % NU == 0, "group rows");
+#pragma unroll 1
     for (int r0 = 0; r0 < NUT; r0 += NU) {
       uint4 ev[NU];
 #pragma unroll
       for (int r = 0; r < NU; ++r) {
-        const int q = tid + NT * (r0 + r), o = q / (D / 8), u = q % (D / 8);
-        const int byte = Wb[o + u / (EPB / 8)];
-        ev[r] = *reinterpret_cast<const uint4*>(E + byte * EPB + (u % (EPB / 8)) * 8);
+        const int q = tid + NT * (r0 + r), o = q / NUR, u = q % NUR;
+        const int byte = Wb[o + u / UPB];
+        ev[r] = *reinterpret_cast<const uint4*>(E + byte * EPB + (u % UPB) * EPU);
       }
 #pragma unroll
       for (int r = 0; r < NU; ++r) {
-        const int q = tid + NT * (r0 + r), o = q / (D / 8), u = q % (D / 8);
+        const int q = tid + NT * (r0 + r), o = q / NUR, u = q % NUR;
         *(uint4*)(Xg + o * XSTR + 16 * (u ^ (o & XM))) = ev[r];
       }
     }
@@ -195,7 +210,8 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_wh(AttnArgs a, int64_t t0, 
       if (lane + 64 * i < S::PWS / 4) *reinterpret_cast<float4*>(pw + 4 * (lane + 64 * i)) = v[i];
   };
 
-  uint2 opk[HPW][NP][NWF][2];  // O of this wave's heads, bf16
+  typedef typename std::conditional<BF, uint2, f32x4>::type OQ;
+  OQ opk[HPW][NP][NWF][2];  // O of this wave's heads as operand values
 #pragma unroll
   for (int hp = 0; hp < HPW; ++hp) {
     const int h = wave * HPW + hp;
@@ -379,11 +395,16 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_wh(AttnArgs a, int64_t t0, 
       for (int nf = 0; nf < NWF; ++nf)
 #pragma unroll
         for (int fr = 0; fr < 2; ++fr) {
-          uint32_t lo = pack_bf16x2(o[nf][fr][0], o[nf][fr][1]), hi = pack_bf16x2(o[nf][fr][2], o[nf][fr][3]);
           // formed here: left to the compiler, the sums sink to their use behind
           // the next head's products and spill the value rows
-          asm volatile("" : "+v"(lo), "+v"(hi));
-          opk[hp][part][nf][fr] = make_uint2(lo, hi);
+          if constexpr (BF) {
+            uint32_t lo = pack_bf16x2(o[nf][fr][0], o[nf][fr][1]), hi = pack_bf16x2(o[nf][fr][2], o[nf][fr][3]);
+            asm volatile("" : "+v"(lo), "+v"(hi));
+            opk[hp][part][nf][fr] = make_uint2(lo, hi);
+          } else {
+            asm volatile("" : "+v"(o[nf][fr]));
+            opk[hp][part][nf][fr] = o[nf][fr];
+          }
         }
     }
     __builtin_amdgcn_wave_barrier();  // (the rows of P.Wv are read)
@@ -399,8 +420,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_wh(AttnArgs a, int64_t t0, 
         for (int fr = 0; fr < 2; ++fr) {
           const int m = 16 * nf + lc;
           const int oe = (wave * HPW + hp) * DH + part * 32 + 16 * fr + 4 * lg;
-          *reinterpret_cast<uint2*>(Xg + m * XSTR + 16 * ((oe >> 3) ^ (m & XM)) + 8 * ((oe >> 2) & 1)) =
-              opk[hp][part][nf][fr];
+          *reinterpret_cast<OQ*>(Xg + m * XSTR + 16 * ((oe / EPU) ^ (m & XM)) + (oe % EPU) * ES) = opk[hp][part][nf][fr];
         }
   __syncthreads();
 
@@ -439,16 +459,16 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_wh(AttnArgs a, int64_t t0, 
   for (int qi = 0; qi < QFW; ++qi) {
     const int d = (wave * QFW + qi) * 16 + 4 * lg;
     const int j = d / EPB, cc = d - j * EPB;
-    const uint2 pb = *reinterpret_cast<const uint2*>(P + (T - 1) * D + d);
+    const f32x4 pb = four(P + (T - 1) * D + d);
 #pragma unroll
     for (int nf = 0; nf < NWF; ++nf) {
       const int m = 16 * nf + lc;
-      const uint2 eb = *reinterpret_cast<const uint2*>(E + Wb[m + QOFF + j] * EPB + cc);
+      const f32x4 eb = four(E + Wb[m + QOFF + j] * EPB + cc);
       float4 r;
-      r.x = acc[qi][nf][0] + (__uint_as_float(eb.x << 16) + __uint_as_float(pb.x << 16));
-      r.y = acc[qi][nf][1] + (__uint_as_float(eb.x & 0xffff0000u) + __uint_as_float(pb.x & 0xffff0000u));
-      r.z = acc[qi][nf][2] + (__uint_as_float(eb.y << 16) + __uint_as_float(pb.y << 16));
-      r.w = acc[qi][nf][3] + (__uint_as_float(eb.y & 0xffff0000u) + __uint_as_float(pb.y & 0xffff0000u));
+      r.x = acc[qi][nf][0] + (eb[0] + pb[0]);
+      r.y = acc[qi][nf][1] + (eb[1] + pb[1]);
+      r.z = acc[qi][nf][2] + (eb[2] + pb[2]);
+      r.w = acc[qi][nf][3] + (eb[3] + pb[3]);
       *reinterpret_cast<float4*>(Hs + m * HSTR + d) = r;
     }
   }
@@ -461,48 +481,58 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_wh(AttnArgs a, int64_t t0, 
   }
 }
 
-template <int T, int G, int D, int DH, int NW>
+template <bool BF, int T, int G, int D, int DH, int NW>
 void launch_nw(const AttnArgs& a, int64_t t0, int tps, int64_t tiles, hipStream_t s) {
-  hipLaunchKernelGGL((k_attn_wh<T, G, D, DH, NW>), dim3((unsigned)tiles), dim3(64 * NW), 0, s, a, t0, tps);
+  hipLaunchKernelGGL((k_attn_wh<BF, T, G, D, DH, NW>), dim3((unsigned)tiles), dim3(64 * NW), 0, s, a, t0, tps);
 }
 
-template <int T, int G, int D, int DH>
+template <bool BF, int T, int G, int D, int DH>
 void launch(const AttnArgs& a, hipStream_t s) {
   // one block per 64 positions of a stream, from the launch's first window's tile
   // to its last window's
+  constexpr int H = D / DH;
   const int tps = (a.w.n_steps + 63) / 64;
   auto tile = [&](int64_t n) { return n / a.w.n_steps * tps + n % a.w.n_steps / 64; };
   const int64_t t0 = tile(a.w.n0), tiles = tile(a.w.n0 + a.w.N - 1) - t0 + 1;
-  if constexpr (D == 512) {
-    launch_nw<T, G, D, DH, 8>(a, t0, tps, tiles, s);
+  if constexpr (H <= 4) {
+    launch_nw<BF, T, G, D, DH, H>(a, t0, tps, tiles, s);
+  } else if constexpr (D * WhShape<BF, T, G, D, DH, 8>::ES == 1024) {
+    launch_nw<BF, T, G, D, DH, 8>(a, t0, tps, tiles, s);
   } else {
     // at most one tile per CU: the tile's own latency counts, and eight waves of
     // one head each take less than four of two (64 tiles at d = 256: 21 / 28 us)
-    if constexpr (D / DH == 8) {
-      if (tiles <= 256) return launch_nw<T, G, D, DH, 8>(a, t0, tps, tiles, s);
-    }
-    launch_nw<T, G, D, DH, 4>(a, t0, tps, tiles, s);
+    if (tiles <= 256) return launch_nw<BF, T, G, D, DH, 8>(a, t0, tps, tiles, s);
+    launch_nw<BF, T, G, D, DH, 4>(a, t0, tps, tiles, s);
   }
 }
 
 }  // namespace
 
-bool launch_attn_wh(int T, int D, int DH, const AttnArgs& a, hipStream_t s) {
+bool launch_attn_wh(bool bf, int T, int D, int DH, const AttnArgs& a, hipStream_t s) {
   // Where a stream's run of positions fills its tiles badly, the per-token
   // kernel: it projects T + 1 rows a window (the last one twice: q and Wo) and a
   // tile here NR + 64, filled or not.  Measured (us, this / per token) on 1021
   // streams: T = 8, g = 8, d = 256 (line at 22 positions): 16 positions 71 / 64,
   // 24 74 / 103; d = 512: 205 / 183, 217 / 268; T = 8, g = 4, d = 128 (line at 18):
-  // 30 / 26, 32 / 46.  The rule looks at the whole call, so chunks agree.
+  // 30 / 26, 32 / 46; fp32 at 24 positions, d = 128: 102 / 173.
+  // Small calls of narrow models are the per-token kernel's too: its 16- and
+  // 32-window tiles spread them over more CUs, and a tile here has only as many
+  // waves as heads.  d = 128: 4096 windows 14 / 13 (fp32 33 / 30), 12992 17 / 26
+  // (36 / 90); d = 64 (one head): 16384 33 / 20, 32768 35 / 38.
+  // The rules look at the whole call, so its chunks agree.
   const int tps = (a.w.n_steps + 63) / 64, nr = (64 + (T - 1) * a.g + 15) / 16 * 16;
   if ((int64_t)a.w.n_steps * (T + 1) < (int64_t)tps * (nr + 64)) return false;
-#define TRACE_WH(T_, G_, D_, DH_)                      \
-  if (T == T_ && a.g == G_ && D == D_ && DH == DH_) {  \
-    launch<T_, G_, D_, DH_>(a, s);                     \
-    return true;                                       \
+  if (D <= 128 && a.total <= (D == 64 ? 24576 : 6144)) return false;
+#define TRACE_WH(BF_, T_, G_, D_, DH_)                             \
+  if (bf == BF_ && T == T_ && a.g == G_ && D == D_ && DH == DH_) { \
+    launch<BF_, T_, G_, D_, DH_>(a, s);                            \
+    return true;                                                   \
   }
-#define TRACE_WH4(D_, DH_) TRACE_WH(8, 8, D_, DH_) TRACE_WH(8, 4, D_, DH_) TRACE_WH(4, 8, D_, DH_) TRACE_WH(4, 4, D_, DH_)
-  TRACE_WH4(128, 32) TRACE_WH4(256, 32) TRACE_WH4(256, 64) TRACE_WH4(512, 64)
+#define TRACE_WH4(BF_, D_, DH_) \
+  TRACE_WH(BF_, 8, 8, D_, DH_) TRACE_WH(BF_, 8, 4, D_, DH_) TRACE_WH(BF_, 4, 8, D_, DH_) TRACE_WH(BF_, 4, 4, D_, DH_)
+  TRACE_WH4(true, 128, 32) TRACE_WH4(true, 128, 64) TRACE_WH4(true, 256, 32) TRACE_WH4(true, 256, 64) TRACE_WH4(true, 512, 64)
+  TRACE_WH4(false, 64, 32) TRACE_WH4(false, 64, 64) TRACE_WH4(false, 128, 32) TRACE_WH4(false, 128, 64)
+  TRACE_WH4(false, 256, 32) TRACE_WH4(false, 256, 64)
 #undef TRACE_WH4
 #undef TRACE_WH
   return false;

@@ -24,6 +24,7 @@ struct AttnArgs {
   float scale;                     // 1/sqrt(head width)
   float scale4;                    // (head width)^-1/4 (Performer)
   int32_t token_only;              // 1: the per-token kernel whatever the launch shape
+  int64_t total;                   // windows of the whole call (its chunks take the same kernel)
   const float* Xin;                // later layers: input rows [N][T][D] (fp32; NULL: byte-group tokens)
   const uint4* Om;                 // Performer: packed random projection (NULL: softmax attention)
   int32_t nfeat;                   // Performer: features (a multiple of 16)
@@ -57,9 +58,9 @@ typedef void (*ffn_fn)(const FfnArgs&, hipStream_t);
 
 // NULL when no kernel is built for the shape.
 attn_fn find_attn(bool bf, int T, int D, int DH);
-// attn_wh.hip: bf16, byte groups shared between the windows of 64-position tiles
+// attn_wh.hip: byte groups shared between the windows of 64-position tiles
 // of each stream; false when the shape is not built
-bool launch_attn_wh(int T, int D, int DH, const AttnArgs& a, hipStream_t s);
+bool launch_attn_wh(bool bf, int T, int D, int DH, const AttnArgs& a, hipStream_t s);
 ffn_fn find_ffn(bool bf, int D);
 
 void launch_zero(void* p, int64_t n32, hipStream_t s);
