@@ -320,7 +320,6 @@ GemmArgs gemm(int M, int N, int K, const float* A, int64_t sam, int64_t sak, int
   g.halfA = g.halfB = g.halfC = 0;
   g.rowwise = 0;
   g.defer = nullptr;
-  g.Cin = nullptr;
   g.r1c = nullptr;
   g.r1tsh = g.r1dsh = g.r1H = g.r1round = 0;
   g.r1scale = 1.f;

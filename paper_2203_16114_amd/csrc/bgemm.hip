@@ -286,8 +286,7 @@ __device__ __forceinline__ int tile_of_block() {
 template <bool AKC, bool BKC, bool SA, bool SB, bool HA, bool HB>
 __device__ __forceinline__ void bgemm_tile(uint4 (&lds)[2][2 + SA + SB][UNITS], int L, const Src& A, const Src& B, int Kp,
                                            int M, int N, float* C, int64_t ldc, float beta, float* __restrict__ part,
-                                           int kchunk, int tn, int tm, const float* __restrict__ gu, int hc,
-                                           const float* cin) {
+                                           int kchunk, int tn, int tm, const float* __restrict__ gu, int hc) {
   static_assert(!(SA && SB), "at most one operand is split");
   constexpr int NT = 2 + (SA ? 1 : 0) + (SB ? 1 : 0);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lg = lane >> 4, lc = lane & 15;
@@ -373,7 +372,7 @@ __device__ __forceinline__ void bgemm_tile(uint4 (&lds)[2][2 + SA + SB][UNITS], 
         }
       }
   } else {
-    // with beta = 1, all the values of Cin (which may be C) are read before any
+    // with beta = 1, all the values of C are read before any
     // C is written
     if (beta != 0.f) {  // clamped addresses, as for gu below
 #pragma unroll
@@ -383,7 +382,7 @@ __device__ __forceinline__ void bgemm_tile(uint4 (&lds)[2][2 + SA + SB][UNITS], 
         for (int r = 0; r < 4; ++r) {
           const int64_t mo = (int64_t)min(mb + rf * 16 + r, M - 1) * ldc;
 #pragma unroll
-          for (int nf = 0; nf < 4; ++nf) c[r][nf] = cin[mo + min(nbase + nf * 16, N - 1)];
+          for (int nf = 0; nf < 4; ++nf) c[r][nf] = C[mo + min(nbase + nf * 16, N - 1)];
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -434,10 +433,9 @@ __device__ __forceinline__ void bgemm_tile(uint4 (&lds)[2][2 + SA + SB][UNITS], 
 template <bool AKC, bool BKC, bool SA, bool SB, bool HA, bool HB>
 __global__ __launch_bounds__(256) void k_bgemm(Src A, Src B, int Kp, int M, int N, float* C, int64_t ldc,
                                                float beta, float* __restrict__ part, int kchunk, int tn, int tm,
-                                               const float* __restrict__ gu, int hc, const float* cin) {
+                                               const float* __restrict__ gu, int hc) {
   __shared__ uint4 lds[2][2 + SA + SB][UNITS];
-  bgemm_tile<AKC, BKC, SA, SB, HA, HB>(lds, tile_of_block(), A, B, Kp, M, N, C, ldc, beta, part, kchunk, tn, tm, gu, hc,
-                                       cin);
+  bgemm_tile<AKC, BKC, SA, SB, HA, HB>(lds, tile_of_block(), A, B, Kp, M, N, C, ldc, beta, part, kchunk, tn, tm, gu, hc);
 }
 
 // Several weight gradients (rows of both operands contiguous, neither split) in
@@ -462,13 +460,13 @@ __global__ __launch_bounds__(256) void k_bgemm_group(BGroup g) {
   const int t = L - j.tile0;
   if (j.mode == 3)
     bgemm_tile<false, false, false, false, true, true>(lds, t, j.A, j.B, j.Kp, j.M, j.N, j.C, j.ldc, 0.f, j.part, j.kchunk,
-                                                       j.tn, j.tm, nullptr, 0, nullptr);
+                                                       j.tn, j.tm, nullptr, 0);
   else if (j.mode == 1)
     bgemm_tile<false, false, false, false, true, false>(lds, t, j.A, j.B, j.Kp, j.M, j.N, j.C, j.ldc, 0.f, j.part,
-                                                        j.kchunk, j.tn, j.tm, nullptr, 0, nullptr);
+                                                        j.kchunk, j.tn, j.tm, nullptr, 0);
   else
     bgemm_tile<false, false, false, false, false, false>(lds, t, j.A, j.B, j.Kp, j.M, j.N, j.C, j.ldc, 0.f, j.part,
-                                                         j.kchunk, j.tn, j.tm, nullptr, 0, nullptr);
+                                                         j.kchunk, j.tn, j.tm, nullptr, 0);
 }
 
 // ---- 256 x 256 tiles, 512 threads (8 waves, two per SIMD), 32 k per stage ----
@@ -665,7 +663,7 @@ __device__ __forceinline__ void store(const float4 (&v)[4], uint32_t mask, uint4
 template <bool AKC, bool BKC, bool SA, bool SB, bool HA, bool HB, int PD>
 __global__ __launch_bounds__(512) void k_bgemm_big(Src A, Src B, int Kp, int M, int N, float* C, int64_t ldc,
                                                    float beta, float* __restrict__ part, int kchunk, int tn, int tm,
-                                                   const float* __restrict__ gu, int hc, const float* cin) {
+                                                   const float* __restrict__ gu, int hc) {
   static_assert(!(SA && SB), "at most one operand is split");
   static_assert(PD == 1 || PD == 2, "prefetch depth");
   constexpr int NT = 2 + (SA ? 1 : 0) + (SB ? 1 : 0);
@@ -798,7 +796,7 @@ __global__ __launch_bounds__(512) void k_bgemm_big(Src A, Src B, int Kp, int M, 
         for (int r = 0; r < 4; ++r) {
           const int64_t mo = (int64_t)min(mb + rf * 16 + r, M - 1) * ldc;
 #pragma unroll
-          for (int nf = 0; nf < FN; ++nf) c[r][nf] = cin[mo + min(nbase + nf * 16, N - 1)];
+          for (int nf = 0; nf < FN; ++nf) c[r][nf] = C[mo + min(nbase + nf * 16, N - 1)];
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -862,7 +860,7 @@ void launch_orient(bool sa, bool sb, bool ha, bool hb, dim3 grid, const Src& A, 
                    float* part, int kchunk, int tn, int tm, hipStream_t s) {
 #define TRACE_BGEMM(SA_, SB_, HA_, HB_, PD_)                                                                 \
   hipLaunchKernelGGL((k_bgemm_big<AKC, BKC, SA_, SB_, HA_, HB_, PD_>), grid, dim3(512), 0, s, A, B, Kp, g.M, g.N, g.C, \
-                     g.ldc, g.beta, part, kchunk, tn, tm, g.gelu_u, g.halfC, g.Cin ? g.Cin : g.C)
+                     g.ldc, g.beta, part, kchunk, tn, tm, g.gelu_u, g.halfC)
   if (sa) {
     if (hb)
       TRACE_BGEMM(true, false, false, true, 2);
@@ -929,7 +927,7 @@ void launch_orient(bool sa, bool sb, bool ha, bool hb, dim3 grid, const Src& A, 
                    float* part, int kchunk, int tn, int tm, hipStream_t s) {
 #define TRACE_BGEMM(SA_, SB_, HA_, HB_)                                                                       \
   hipLaunchKernelGGL((k_bgemm<AKC, BKC, SA_, SB_, HA_, HB_>), grid, dim3(256), 0, s, A, B, Kp, g.M, g.N, g.C, g.ldc, \
-                     g.beta, part, kchunk, tn, tm, g.gelu_u, g.halfC, g.Cin ? g.Cin : g.C)
+                     g.beta, part, kchunk, tn, tm, g.gelu_u, g.halfC)
   if (sa) {
     if (hb)
       TRACE_BGEMM(true, false, false, true);
@@ -1049,7 +1047,7 @@ bool launch_bgemm(const GemmArgs& g, const GemmArgs* g2, float* ws, int64_t ws_c
     g.defer->pstride = (int64_t)g.M * g.N;
     g.defer->splits = splits;
   } else if (splits > 1) {
-    launch_splitk_reduce(ws, splits, g.M, g.N, g.C, g.ldc, g.beta, g.Cin, s);
+    launch_splitk_reduce(ws, splits, g.M, g.N, g.C, g.ldc, g.beta, s);
   }
   return true;
 }

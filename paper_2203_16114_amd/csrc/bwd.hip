@@ -106,14 +106,14 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g, float* __restrict__ pa
 
 // C(m,n) = [C(m,n) +] sum_z part[z][m][n], z in increasing order.
 __global__ void k_splitk_reduce(const float* __restrict__ part, int splits, int M, int N, float* C, int64_t ldc,
-                                float beta, const float* cin) {
+                                float beta) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= (int64_t)M * N) return;
   const int m = (int)(i / N), n = (int)(i % N);
   float s = 0.f;
   for (int z = 0; z < splits; ++z) s += part[((int64_t)z * M + m) * N + n];
   const int64_t o = (int64_t)m * ldc + n;
-  C[o] = (beta != 0.f) ? (cin[o] + s) : s;
+  C[o] = (beta != 0.f) ? (C[o] + s) : s;
 }
 
 // 128x128-tile GEMM for the two operand layouts of the update: operands whose
@@ -327,9 +327,9 @@ static void launch128(const GemmArgs& g, float* part, int kchunk, dim3 grid, hip
 
 // Four consecutive n per thread (one float4 of C and of each partial), eight
 // partials in flight; the same sum order (z increasing, then the addend) as
-// k_splitk_reduce.  Needs N, ldc multiples of 4 and 16-byte aligned C, cin.
+// k_splitk_reduce.  Needs N, ldc multiples of 4 and 16-byte aligned C.
 __global__ __launch_bounds__(256) void k_splitk_reduce4(const float* __restrict__ part, int splits, int M, int N,
-                                                        float* C, int64_t ldc, float beta, const float* cin) {
+                                                        float* C, int64_t ldc, float beta) {
   const uint32_t q = blockIdx.x * 256u + threadIdx.x, n4 = (uint32_t)N >> 2;
   if (q >= (uint32_t)M * n4) return;
   const uint32_t m = q / n4, n = (q - m * n4) * 4;
@@ -352,21 +352,19 @@ __global__ __launch_bounds__(256) void k_splitk_reduce4(const float* __restrict_
   }
   for (; z < splits; ++z) add(*reinterpret_cast<const float4*>(p + (int64_t)z * MN));
   const int64_t o = (int64_t)m * ldc + n;
-  if (beta != 0.f) add(*reinterpret_cast<const float4*>(cin + o));
+  if (beta != 0.f) add(*reinterpret_cast<const float4*>(C + o));
   *reinterpret_cast<float4*>(C + o) = s;
 }
 
 void launch_splitk_reduce(const float* ws, int splits, int M, int N, float* C, int64_t ldc, float beta,
-                          const float* cin, hipStream_t s) {
-  if (!cin) cin = C;
+                          hipStream_t s) {
   const int64_t tot = (int64_t)M * N;
-  if (N % 4 == 0 && ldc % 4 == 0 && ((uintptr_t)ws & 15) == 0 && ((uintptr_t)C & 15) == 0 &&
-      ((uintptr_t)cin & 15) == 0)
+  if (N % 4 == 0 && ldc % 4 == 0 && ((uintptr_t)ws & 15) == 0 && ((uintptr_t)C & 15) == 0)
     hipLaunchKernelGGL(k_splitk_reduce4, dim3((unsigned)((tot / 4 + 255) / 256)), dim3(256), 0, s, ws, splits, M, N, C,
-                       ldc, beta, cin);
+                       ldc, beta);
   else
     hipLaunchKernelGGL(k_splitk_reduce, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, ws, splits, M, N, C, ldc,
-                       beta, cin);
+                       beta);
 }
 
 // Several split-K sums and positional parts in one launch (RedJob), four
@@ -483,11 +481,6 @@ bool launch_gemm(const GemmArgs& g0, float* ws, int64_t ws_cap, hipStream_t s) {
   // the kernels below use fp32 operands and results, and read B as stored
   if (g0.halfA || g0.halfB || g0.halfC || g0.r1c) return false;
   GemmArgs g = g0;
-  if (g.Cin && g.Cin != g.C && g.beta != 0.f) {  // the kernels below add C itself: the addend goes there first
-    (void)hipMemcpy2DAsync(g.C, (size_t)g.ldc * 4, g.Cin, (size_t)g.ldc * 4, (size_t)g.N * 4, (size_t)g.M,
-                           hipMemcpyDeviceToDevice, s);
-  }
-  g.Cin = nullptr;
   if (g.gelu_u) {  // the product, then the GELU derivative in place (C laid out densely, as gelu_u)
     GemmArgs h = g;
     h.gelu_u = nullptr;
@@ -520,7 +513,7 @@ bool launch_gemm(const GemmArgs& g0, float* ws, int64_t ws_cap, hipStream_t s) {
     else
       hipLaunchKernelGGL(k_gemm<false>, grid, dim3(256), 0, s, g, part, kchunk);
   }
-  if (splits > 1) launch_splitk_reduce(ws, splits, g.M, g.N, g.C, g.ldc, g.beta, nullptr, s);
+  if (splits > 1) launch_splitk_reduce(ws, splits, g.M, g.N, g.C, g.ldc, g.beta, s);
   return true;
 }
 
@@ -1568,7 +1561,7 @@ bool launch_kv_wgrad(const uint16_t* X, const uint8_t* win, const uint16_t* E, i
       red[i].ldc = D;
     }
   } else {
-    launch_splitk_reduce(ws, S, 2 * D, D, dWk, D, 0.f, nullptr, s);
+    launch_splitk_reduce(ws, S, 2 * D, D, dWk, D, 0.f, s);
   }
   return true;
 }

@@ -241,7 +241,7 @@ bool launch_fgemm(const GemmArgs& g, const GemmArgs* g2, float* ws, int64_t ws_c
   a.N = g.N;
   a.C = g.C;
   a.ldc = g.ldc;
-  a.cin = g.beta != 0.f ? (g.Cin ? g.Cin : g.C) : nullptr;
+  a.cin = g.beta != 0.f ? g.C : nullptr;
   a.gu = g.gelu_u;
   const int64_t big = (int64_t)((g.M + 31) / 32) * ((g.N + 31) / 32);
   const bool wide = big >= 256;
@@ -257,7 +257,7 @@ bool launch_fgemm(const GemmArgs& g, const GemmArgs* g2, float* ws, int64_t ws_c
     launch<2, 2>(akc, bkc, a, grid, s);
   else
     launch<1, 4>(akc, bkc, a, grid, s);
-  if (z > 1) launch_splitk_reduce(ws, z, g.M, g.N, g.C, g.ldc, g.beta, g.Cin, s);
+  if (z > 1) launch_splitk_reduce(ws, z, g.M, g.N, g.C, g.ldc, g.beta, s);
   return true;
 }
 

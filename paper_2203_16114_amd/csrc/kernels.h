@@ -116,9 +116,7 @@ struct GemmArgs {
   float* C;
   int64_t ldc;       // C(m,n) = C[m*ldc + n]
   int roundA, roundB;  // round that operand to bf16 (RNE) as it is read
-  float beta;          // C = beta*Cin + A.B  (beta 0 or 1)
-  // nullable: the addend of beta (laid out as C, ldc apart); NULL: C itself
-  const float* Cin;
+  float beta;          // C = beta*C + A.B  (beta 0 or 1)
   // nullable: B formed from rank-one rows, B(k, n) = (r1c[(w H + n / dh) T + t] . V(w, n)) . r1scale
   // for k = w T + t, with V(w, n) = B[w*sbk + n] (sbn = 1; rounded to bf16 first if r1round) and
   // T = 2^r1tsh, dh = 2^r1dsh, H = r1H (the key and value gradients of the last query row);
@@ -160,7 +158,7 @@ bool launch_gemm(const GemmArgs& g, float* ws, int64_t ws_cap, hipStream_t s);
 // flags; one launch when the bf16 kernel takes both, else two
 void launch_gemm2(const GemmArgs& g, const GemmArgs& g2, float* ws, int64_t ws_cap, hipStream_t s);
 void launch_splitk_reduce(const float* ws, int splits, int M, int N, float* C, int64_t ldc, float beta,
-                          const float* cin, hipStream_t s);
+                          hipStream_t s);
 // bgemm.hip: false (nothing launched) when the product is not one it takes;
 // g2 (nullable) is a second K segment summed into the same result
 // force: 0 the kernel the shape calls for, 1 the 128-tile kernel, 2 the 256-tile kernel
