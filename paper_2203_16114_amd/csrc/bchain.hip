@@ -191,6 +191,11 @@ __global__ __launch_bounds__((D >= 128 ? 512 : 256)) void k_bwd_chain(ChainArgs 
     const uint4* W2p = a.W2T + r * a.wstride;
     const uint4* W1p = a.W1T + r * a.wstride;
     put_y(r + 1);
+    // fp32: the repeat's product is summed from zero and added to dY_{r+1} once (its
+    // terms are far smaller than dY: summed onto it, each would be rounded at dY's size)
+    f32x4 yf[RF2][NFC];
+    if constexpr (!BF) zero(yf);
+    f32x4(&ya)[RF2][NFC] = BF ? y : yf;
     __syncthreads();
     for (int c0 = 0; c0 < F; c0 += FC) {
 #pragma unroll
@@ -266,10 +271,16 @@ __global__ __launch_bounds__((D >= 128 ? 512 : 256)) void k_bwd_chain(ChainArgs 
 #pragma unroll
         for (int rf = 0; rf < RF2; ++rf)
 #pragma unroll
-          for (int nf = 0; nf < NFC; ++nf) M::run(y[rf][nf], wb[ks][rf], bb[ks % (PL + 1)][nf]);
+          for (int nf = 0; nf < NFC; ++nf) M::run(ya[rf][nf], wb[ks][rf], bb[ks % (PL + 1)][nf]);
         __builtin_amdgcn_sched_barrier(0);
       }
       __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (!BF) {
+#pragma unroll
+      for (int rf = 0; rf < RF2; ++rf)
+#pragma unroll
+        for (int nf = 0; nf < NFC; ++nf) y[rf][nf] += yf[rf][nf];
     }
   }
   put_y(0);
