@@ -1204,13 +1204,14 @@ extern "C" int trace_read_timing(trace_model* m, double* ms_total, int64_t* laun
 namespace {
 // Host threads kept for one compress or decompress call: run(n, fn) calls
 // fn(b0, b1) over [0, n) in contiguous pieces, one per thread (one thread
-// below 512 items, up to 16), and returns when all pieces are done.  Each item
-// is written by one thread only.
+// below 4096 items, up to 16), and returns when all pieces are done.  Each item
+// is written by one thread only.  An item, one stream's O(1) coder step, takes
+// about 15 ns, waking the threads tens of us.
 class WorkPool {
  public:
   explicit WorkPool(int64_t n_items) {
     const int64_t hw = std::max<int64_t>(1, std::min<int64_t>(16, (int64_t)std::thread::hardware_concurrency()));
-    nt_ = n_items < 512 ? 1 : std::min<int64_t>(hw, n_items / 256);
+    nt_ = n_items < 4096 ? 1 : std::min<int64_t>(hw, n_items / 2048);
     for (int64_t t = 1; t < nt_; ++t) th_.emplace_back([this, t] { worker(t); });
   }
   ~WorkPool() {
@@ -1337,57 +1338,65 @@ extern "C" int trace_rc_decode(const uint16_t* freq, int64_t freq_stride, const 
 }
 
 namespace {
+// log2 of the integers up to 65536 (host, computed once)
+const double* log2_table() {
+  static const std::vector<double> t = [] {
+    std::vector<double> v(65537);
+    for (int i = 1; i <= 65536; ++i) v[i] = std::log2((double)i);
+    return v;
+  }();
+  return t.data();
+}
+
 // The loop of Alg. 1 shared by both directions over n_streams streams of
-// `length` bytes: bytes [0, W) at 1/256 (lines 1-5); at each i >= W one
-// forward over the windows ending before i (line 8) -> frequencies -> the
-// coding step code(i, freq) (line 9, which leaves the bytes at i in h) -> the
-// controller on the batch-mean coded length (Alg. 2) -> if it says so, the
+// `length` bytes, past the first W of them (lines 6-11): at each i >= W one
+// forward over the windows ending before i (line 8) -> launch(logits, i, coded),
+// which leaves each stream's coded byte in host memory and, in d_src, the bytes at
+// i -> the controller on the batch-mean coded length (Alg. 2) -> if it says so, the
 // forward again keeping activations and the backward + Adam (line 10).
-// d_src holds the bytes the forwards read; after code(i) its column i holds
-// the bytes at i (the targets of the keeping forward).
-template <class First, class Code>
+// advance(coded) brings the coders past the byte (line 9): on the host, after the
+// update and the next forward are on their way.
+template <class Launch, class Advance>
 int coding_loop(trace_model* m, const uint8_t* d_src, int64_t stride, int32_t B, int64_t length, int32_t mode,
-                int32_t ctl_t, double ctl_delta, int64_t* n_updates, void* stream, First first, Code code) {
+                trace_controller* ctl, int64_t* n_updates, void* stream, Launch launch, Advance advance) {
   const int W = m->cfg.W;
   hipStream_t s = (hipStream_t)stream;
-  trace_controller ctl;
-  if (mode == 1) {
-    const int rc = trace_controller_init(&ctl, ctl_t, ctl_delta);
-    if (rc) return rc;
-  }
-  int rc = first((int64_t)std::min<int64_t>(W, length));
-  if (rc) return rc;
-  if (length <= W) {
-    if (n_updates) *n_updates = 0;
-    return TRACE_OK;
-  }
-  float *d_logits = nullptr, *d_bits = nullptr;
-  uint16_t* d_freq = nullptr;
-  hipError_t e = hipMalloc(&d_logits, (size_t)B * 256 * 4);
-  if (e == hipSuccess) e = hipMalloc(&d_bits, (size_t)B * 4);
-  if (e == hipSuccess) e = hipMalloc(&d_freq, (size_t)B * 256 * 2);
-  // frequencies land in pinned host memory (one direct copy per position)
-  uint16_t* hf = nullptr;
-  if (e == hipSuccess) e = hipHostMalloc((void**)&hf, (size_t)B * 256 * 2, hipHostMallocDefault);
+  if (n_updates) *n_updates = 0;
+  if (length <= W) return TRACE_OK;
+  const double* lg = log2_table();
+  float* d_logits = nullptr;  // and the code lengths
+  CodedByte* coded = nullptr;
+  hipError_t e = hipMalloc(&d_logits, (size_t)B * 257 * 4);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&coded, (size_t)B * sizeof(CodedByte), hipHostMallocDefault);
   int64_t updates = 0;
-  rc = e == hipSuccess ? TRACE_OK : hip_fail(e, "coding buffers");
+  int rc = e == hipSuccess ? TRACE_OK : hip_fail(e, "coding buffers");
+  float* d_bits = d_logits + (size_t)B * 256;
+  auto forward = [&](int64_t i) {
+    return trace_forward_bits(m, d_src, stride, B, i, 1, d_bits, d_logits, nullptr, 0, stream);
+  };
+  if (rc == TRACE_OK) rc = forward(W);
   for (int64_t i = W; i < length && rc == TRACE_OK; ++i) {
-    rc = trace_forward_bits(m, d_src, stride, B, i, 1, d_bits, d_logits, nullptr, 0, stream);
-    if (rc) break;
-    launch_quantize(d_logits, B, d_freq, s);
-    e = hipMemcpyAsync(hf, d_freq, (size_t)B * 256 * 2, hipMemcpyDeviceToHost, s);
+    launch(d_logits, i, coded);
+    e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
       rc = hip_fail(e, "coding step");
       break;
     }
     double ce = 0.0;
-    rc = code(i, hf, &ce);
-    if (rc) break;
+    bool valid = true;
+    for (int32_t b = 0; b < B; ++b) {  // streams in order
+      valid = valid && coded[b].f > 0;
+      ce += lg[coded[b].total] - lg[coded[b].f];
+    }
+    if (!valid) {
+      rc = fail(TRACE_ESTATE, "the model's logits are not finite: no code intervals");
+      break;
+    }
     ce /= B;
     int32_t upd = mode == 2 ? 1 : 0;
     if (mode == 1) {
-      rc = trace_controller_decide(&ctl, ce, &upd);
+      rc = trace_controller_decide(ctl, ce, &upd);
       if (rc) break;
     }
     if (upd) {
@@ -1395,11 +1404,12 @@ int coding_loop(trace_model* m, const uint8_t* d_src, int64_t stride, int32_t B,
       if (!rc) rc = trace_adapt_step(m, stream);
       ++updates;
     }
+    if (rc == TRACE_OK && i + 1 < length) rc = forward(i + 1);
+    advance(coded);
   }
+  if (rc != TRACE_OK) (void)hipStreamSynchronize(s);
   hipFree(d_logits);
-  hipFree(d_bits);
-  hipFree(d_freq);
-  if (hf) hipHostFree(hf);
+  if (coded) hipHostFree(coded);
   if (n_updates) *n_updates = updates;
   return rc;
 }
@@ -1413,16 +1423,9 @@ int coding_args(trace_model* m, int32_t B, int64_t length, int64_t stride, int32
   return TRACE_OK;
 }
 
-// coded length of byte x under one frequency row, log2(total) - log2(freq[x])
-double coded_bits(const uint16_t* f, int x, uint32_t* cum_out, uint32_t* tot_out) {
-  uint32_t cum = 0, tot = 0;
-  for (int v = 0; v < 256; ++v) {
-    if (v < x) cum += f[v];
-    tot += f[v];
-  }
-  *cum_out = cum;
-  *tot_out = tot;
-  return std::log2((double)tot) - std::log2((double)f[x]);
+// the controller of a coding call, whose arguments are wrong before any work
+int coding_controller(int32_t mode, int32_t ctl_t, double ctl_delta, trace_controller* ctl) {
+  return mode == 1 ? trace_controller_init(ctl, ctl_t, ctl_delta) : TRACE_OK;
 }
 }  // namespace
 
@@ -1529,46 +1532,42 @@ extern "C" int trace_compress(trace_model* m, const uint8_t* d_streams, int64_t 
   if (rc) return rc;
   if (!d_streams || !out || !out_sizes || out_stride < 1) return fail(TRACE_EINVAL, "NULL buffer or out_stride < 1");
   const int32_t B = n_streams;
-  std::vector<uint8_t> h((size_t)B * length);
+  trace_controller ctl;
+  // the bytes before the first window's end, at 1/256 (lines 1-5)
+  const int64_t n0 = std::min<int64_t>(m->cfg.W, length);
+  std::vector<uint8_t> h((size_t)B * n0);
   hipStream_t s = (hipStream_t)stream;
-  if (length > 0) {
+  if (n0 > 0) {
     // rows packed on the device, then one copy (a strided copy to the host
     // moves row by row)
     uint8_t* d_pack = nullptr;
-    hipError_t e = stride == length ? hipSuccess : hipMalloc(&d_pack, (size_t)B * length);
+    hipError_t e = stride == n0 ? hipSuccess : hipMalloc(&d_pack, (size_t)B * n0);
     if (e == hipSuccess && d_pack)
-      e = hipMemcpy2DAsync(d_pack, length, d_streams, stride, length, B, hipMemcpyDeviceToDevice, s);
+      e = hipMemcpy2DAsync(d_pack, n0, d_streams, stride, n0, B, hipMemcpyDeviceToDevice, s);
     if (e == hipSuccess)
-      e = hipMemcpyAsync(h.data(), d_pack ? d_pack : d_streams, (size_t)B * length, hipMemcpyDeviceToHost, s);
+      e = hipMemcpyAsync(h.data(), d_pack ? d_pack : d_streams, (size_t)B * n0, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (d_pack) hipFree(d_pack);
     if (e != hipSuccess) return hip_fail(e, "trace_compress");
   }
+  rc = coding_controller(mode, ctl_t, ctl_delta, &ctl);
+  if (rc) return rc;
   std::vector<RcEnc> enc(B);
   for (int32_t b = 0; b < B; ++b) {
     enc[b].out = out + (int64_t)b * out_stride;
     enc[b].cap = out_stride;
+    for (int64_t i = 0; i < n0; ++i) enc[b].encode(h[(size_t)b * n0 + i], 1, 256);
   }
-  auto first = [&](int64_t n0) {
-    for (int64_t i = 0; i < n0; ++i)
-      for (int32_t b = 0; b < B; ++b) enc[b].encode(h[(size_t)b * length + i], 1, 256);
-    return TRACE_OK;
-  };
-  std::vector<double> cb(B);
   WorkPool pool(B);
-  auto code = [&](int64_t i, const uint16_t* hf, double* ce) {
-    pool.run(B, [&](int64_t b0, int64_t b1) {
-      for (int64_t b = b0; b < b1; ++b) {
-        const int x = h[(size_t)b * length + i];
-        uint32_t cum, tot;
-        cb[b] = coded_bits(hf + (size_t)b * 256, x, &cum, &tot);
-        enc[b].encode(cum, hf[(size_t)b * 256 + x], tot);
-      }
-    });
-    for (int32_t b = 0; b < B; ++b) *ce += cb[b];  // streams in order
-    return TRACE_OK;
+  auto launch = [&](const float* z, int64_t i, CodedByte* coded) {
+    launch_encode_step(z, B, d_streams + i, stride, coded, s);
   };
-  rc = coding_loop(m, d_streams, stride, B, length, mode, ctl_t, ctl_delta, n_updates, stream, first, code);
+  auto advance = [&](const CodedByte* coded) {
+    pool.run(B, [&](int64_t b0, int64_t b1) {
+      for (int64_t b = b0; b < b1; ++b) enc[b].encode(coded[b].cum, coded[b].f, coded[b].total);
+    });
+  };
+  rc = coding_loop(m, d_streams, stride, B, length, mode, &ctl, n_updates, stream, launch, advance);
   if (rc) return rc;
   bool over = false;
   for (int32_t b = 0; b < B; ++b) {
@@ -1589,66 +1588,50 @@ extern "C" int trace_decompress(trace_model* m, const uint8_t* comp, int64_t com
   const int32_t B = n_streams;
   for (int32_t b = 0; b < B; ++b)
     if (comp_sizes[b] < 0 || comp_sizes[b] > comp_stride) return fail(TRACE_EINVAL, "comp_sizes out of range");
-  std::vector<uint8_t> h((size_t)B * std::max<int64_t>(length, 1));
+  trace_controller ctl;
+  rc = coding_controller(mode, ctl_t, ctl_delta, &ctl);
+  if (rc) return rc;
+  // the bytes before the first window's end, at 1/256 (lines 1-5)
+  const int64_t n0 = std::min<int64_t>(m->cfg.W, length);
+  std::vector<uint8_t> h((size_t)B * n0);
   std::vector<RcDec> dec(B);
   for (int32_t b = 0; b < B; ++b) {
     dec[b].in = comp + (int64_t)b * comp_stride;
     dec[b].size = comp_sizes[b];
     dec[b].start();
+    for (int64_t i = 0; i < n0; ++i) h[(size_t)b * n0 + i] = (uint8_t)dec[b].decode_uniform();
   }
   hipStream_t s = (hipStream_t)stream;
-  // columns [i0, i0 + n) of the host copy -> d_out: each column as one
-  // contiguous copy and a scatter into the rows (strided copies of single
-  // bytes are slow)
-  // (pinned, so the copy reads it directly; it is rewritten only after the
-  // next position's synchronisation, which follows this copy on the stream)
-  uint8_t* d_col = nullptr;
-  uint8_t* col = nullptr;
-  hipError_t e0 = hipMalloc(&d_col, (size_t)B);
-  if (e0 == hipSuccess) e0 = hipHostMalloc((void**)&col, (size_t)B, hipHostMallocDefault);
-  if (e0 != hipSuccess) {
-    if (d_col) hipFree(d_col);
-    return hip_fail(e0, "trace_decompress");
+  if (n0 > 0) {  // one copy, then the rows placed on the device
+    uint8_t* d_pack = nullptr;
+    hipError_t e = hipMalloc(&d_pack, (size_t)B * n0);
+    if (e == hipSuccess) e = hipMemcpyAsync(d_pack, h.data(), (size_t)B * n0, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = hipMemcpy2DAsync(d_out, stride, d_pack, n0, n0, B, hipMemcpyDeviceToDevice, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (d_pack) hipFree(d_pack);
+    if (e != hipSuccess) return hip_fail(e, "trace_decompress");
   }
-  auto put_cols = [&](int64_t i0, int64_t n, bool wait) {
-    hipError_t e = hipSuccess;
-    for (int64_t i = i0; i < i0 + n && e == hipSuccess; ++i) {
-      for (int32_t b = 0; b < B; ++b) col[b] = h[(size_t)b * length + i];
-      e = hipMemcpyAsync(d_col, col, (size_t)B, hipMemcpyHostToDevice, s);
-      if (e == hipSuccess) {
-        launch_put_column(d_col, B, d_out, stride, i, s);
-        e = hipGetLastError();
-      }
-      if (e == hipSuccess && (wait || i + 1 < i0 + n)) e = hipStreamSynchronize(s);
-    }
-    return e == hipSuccess ? TRACE_OK : hip_fail(e, "trace_decompress");
-  };
-  auto first = [&](int64_t n0) {
-    for (int64_t i = 0; i < n0; ++i)
-      for (int32_t b = 0; b < B; ++b) h[(size_t)b * length + i] = (uint8_t)dec[b].decode_uniform();
-    return n0 > 0 ? put_cols(0, n0, true) : TRACE_OK;
-  };
-  std::vector<double> cb(B);
+  // the decoders' states as the device reads them (pinned; rewritten after the
+  // synchronisation behind the launch that read them)
+  RcState* state = nullptr;
+  const hipError_t e0 = hipHostMalloc((void**)&state, (size_t)B * sizeof(RcState), hipHostMallocDefault);
+  if (e0 != hipSuccess) return hip_fail(e0, "trace_decompress");
+  for (int32_t b = 0; b < B; ++b) state[b] = RcState{dec[b].range, dec[b].code};
   WorkPool pool(B);
-  auto code = [&](int64_t i, const uint16_t* hf, double* ce) {
+  auto launch = [&](const float* z, int64_t i, CodedByte* coded) {
+    launch_decode_step(z, B, state, d_out + i, stride, coded, s);
+  };
+  auto advance = [&](const CodedByte* coded) {
     pool.run(B, [&](int64_t b0, int64_t b1) {
       for (int64_t b = b0; b < b1; ++b) {
-        const uint16_t* f = hf + (size_t)b * 256;
-        uint32_t tot = 0;
-        for (int v = 0; v < 256; ++v) tot += f[v];
-        const int x = dec[b].decode(f, 256, tot);
-        h[(size_t)b * length + i] = (uint8_t)x;
-        uint32_t cum;
-        cb[b] = coded_bits(f, x, &cum, &tot);
+        dec[b].consume(coded[b].cum, coded[b].f, coded[b].total);
+        state[b] = RcState{dec[b].range, dec[b].code};
       }
     });
-    for (int32_t b = 0; b < B; ++b) *ce += cb[b];  // streams in order
-    return put_cols(i, 1, false);
   };
-  rc = coding_loop(m, d_out, stride, B, length, mode, ctl_t, ctl_delta, n_updates, stream, first, code);
-  const hipError_t e1 = hipStreamSynchronize(s);  // the last column's copy reads col
-  hipFree(d_col);
-  hipHostFree(col);
+  rc = coding_loop(m, d_out, stride, B, length, mode, &ctl, n_updates, stream, launch, advance);
+  const hipError_t e1 = hipStreamSynchronize(s);
+  hipHostFree(state);
   if (rc == TRACE_OK && e1 != hipSuccess) rc = hip_fail(e1, "trace_decompress");
   return rc;
 }

@@ -14,8 +14,21 @@ constexpr int QMAX = 32 * 256 - 1;        // largest fixed-point distance from t
 const uint32_t* quant_table();
 // freq[w][s] for logits z[w][256] of n windows (device), on stream s
 void launch_quantize(const float* z, int64_t n, uint16_t* freq, hipStream_t s);
-// dst[b*stride + col] = src[b], b < n (device)
-void launch_put_column(const uint8_t* src, int64_t n, uint8_t* dst, int64_t stride, int64_t col, hipStream_t s);
+
+// A coded byte of one stream: cumulative frequency, frequency, total, byte.
+struct CodedByte {
+  uint32_t cum, f, total, sym;
+};
+// A decoder's state between two bytes.
+struct RcState {
+  uint32_t range, code;
+};
+// One position of n streams on stream s: the frequencies of z[w][256] and the
+// interval of the byte at bytes[w*stride] (encoder) -> out[w]
+void launch_encode_step(const float* z, int64_t n, const uint8_t* bytes, int64_t stride, CodedByte* out, hipStream_t s);
+// ... or of the byte that state[w] decodes to, also written to bytes[w*stride]
+void launch_decode_step(const float* z, int64_t n, const RcState* state, uint8_t* bytes, int64_t stride, CodedByte* out,
+                        hipStream_t s);
 
 // Encoder: low carries into the byte held back in cache (and the run of 0xFF
 // bytes behind it); the first byte written is 0.  Bytes past cap are counted
@@ -82,13 +95,18 @@ struct RcDec {
       if (v < cum + f[s]) break;
       cum += f[s];
     }
+    consume(cum, f[s], total);
+    return s;
+  }
+  // past the symbol with cumulative frequency cum, frequency f
+  void consume(uint32_t cum, uint32_t f, uint32_t total) {
+    const uint32_t q = range / total;
     code -= q * cum;
-    range = q * f[s];
+    range = q * f;
     while (range < (1u << 24)) {
       code = (code << 8) | next();
       range <<= 8;
     }
-    return s;
   }
   // a byte of probability 1/256
   int decode_uniform() {
